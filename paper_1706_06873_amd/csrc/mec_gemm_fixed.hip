@@ -1612,24 +1612,7 @@ hipError_t dispatch_fixed(const Shape& s, const void* A, const void* K, float* O
         return dry_run ? hipSuccess : run_stream<CFG>(s, A, K, O, stream, layout);  \
     }
     if (dtype == 0) {
-        // tall kernels over short rows of L (11x11 over 3 channels: 33 elements):
-        // the flat windows through a ring of LDS (mec_gemm_ring.hip), where the
-        // ring holds four output rows' windows (strides up to 4 for 11x11).
-        // Measured at batch 32 against the tiles, from L / fused: cv1 stride 3
-        // 207 -> 141 us; 7x7 stride 2 over 3 channels (cv3) 101 / 93 -> 86 us;
-        // 5x5 stride 2 over 3 channels 24 / 30 -> 18 us, over 6 channels 28 /
-        // 28 -> 21 us; fused, rows of at most 10 elements, 3x3 over 3 channels
-        // (vgg_first, cv7) 51 -> 46 us and 93 -> 83 us. From L the ring takes
-        // only windows of at most two blocks (K held in registers, fills five
-        // blocks ahead): with L read from HBM, vgg_first 59 -> 54 us and cv7
-        // 116 -> 99 us against the streaming kernel, which keeps the longer
-        // windows (the ring read those more slowly). At stride 1 with longer
-        // rows it is even or slower (3x3 over 16 channels 92 / 81 -> 92 / 89
-        // us, 5x5 over 8 channels even): those keep the tiles.
-        if (!layout &&
-            (s.k_h >= 9 || (s.k_h >= 5 && s.s_h >= 2) || (s.k_h >= 3 && s.R <= 10 && (F || gemm_ring_short(s)))) &&
-            s.R <= 48 && gemm_ring_usable(s, dtype))
-            return dry_run ? hipSuccess : launch_gemm_ring(s, A, K, O, F, stream);
+        if (gemm_ring_taken(s, dtype, F, layout)) return dry_run ? hipSuccess : launch_gemm_ring(s, A, K, O, F, stream);
         if (s.R >= 32) {
             // no split into a strided layout: zeroing O would clear other pixels
             const TileChoice tc =
@@ -1785,6 +1768,26 @@ hipError_t dispatch_fixed(const Shape& s, const void* A, const void* K, float* O
 }
 
 }  // namespace
+
+// tall kernels over short rows of L (11x11 over 3 channels: 33 elements):
+// the flat windows through a ring of LDS (mec_gemm_ring.hip), where the
+// ring holds four output rows' windows (strides up to 4 for 11x11).
+// Measured at batch 32 against the tiles, from L / fused: cv1 stride 3
+// 207 -> 141 us; 7x7 stride 2 over 3 channels (cv3) 101 / 93 -> 86 us;
+// 5x5 stride 2 over 3 channels 24 / 30 -> 18 us, over 6 channels 28 /
+// 28 -> 21 us; fused, rows of at most 10 elements, 3x3 over 3 channels
+// (vgg_first, cv7) 51 -> 46 us and 93 -> 83 us. From L the ring takes
+// only windows of at most two blocks (K held in registers, fills five
+// blocks ahead): with L read from HBM, vgg_first 59 -> 54 us and cv7
+// 116 -> 99 us against the streaming kernel, which keeps the longer
+// windows (the ring read those more slowly). At stride 1 with longer
+// rows it is even or slower (3x3 over 16 channels 92 / 81 -> 92 / 89
+// us, 5x5 over 8 channels even): those keep the tiles.
+bool gemm_ring_taken(const Shape& s, int dtype, bool fused, const OutLayout* layout) {
+    return dtype == 0 && !layout &&
+           (s.k_h >= 9 || (s.k_h >= 5 && s.s_h >= 2) || (s.k_h >= 3 && s.R <= 10 && (fused || gemm_ring_short(s)))) &&
+           s.R <= 48 && gemm_ring_usable(s, dtype);
+}
 
 hipError_t launch_gemm_fixed(const Shape& s, const void* A, const void* K, float* O, int dtype,
                              bool fused, hipStream_t stream, bool dry_run, const OutLayout* layout) {

@@ -1,0 +1,605 @@
+// The slab products as one implicit matrix product on the bf16 matrix cores,
+// for any kernel height, width, stride and channel count, from L or from I.
+//
+// Row p of the product is output pixel (n, h, w); its reduction runs over nseg
+// runs of seglen consecutive elements of the source, xstride apart:
+//   from L  one run, the window L[n, w][s_h*R*h : s_h*R*h + k_h*R] (Section 3.2),
+//   from I  k_h runs of R = k_w*i_c elements, one per kernel row,
+// so the same code reads either, in the same order: elements j = 0 .. k_h*R - 1 of
+// the window, in chunks of 32.
+//
+// fp32 on bf16 matrix cores. Each fp32 value x is split without loss into three
+// bf16 values, x = hi + mid + lo (hi its upper 8 significant bits, mid the next
+// 8, lo the last 8), and a product is the six bf16 products
+//   hi*hi + (hi*mid + mid*hi) + (hi*lo + mid*mid + lo*hi),
+// each exact in fp32. The three left out (mid*lo, lo*mid, lo*lo) are below
+// 2^-22 of the product, 2^-26 on average. v_mfma_f32_32x32x16_bf16 does
+// 16 times the multiply-adds of v_mfma_f32_32x32x2_f32 in half its cycles per
+// instruction, so six of them still run 2.6 times as many fp32 products. The
+// matrix cores cut sums off at about 2^-24 of the largest addend where the fp32
+// instruction rounds each of its steps, so the five small products go to
+// accumulators of their own, added once at the end. Measured against 64 bits
+// (reductions of 32 to 32768 terms, three distributions): 0.3-0.5 of the fp32
+// instruction's error.
+// Not finite or very small values: an infinity or NaN in a window, and a sum
+// that leaves fp32's range, leave infinities or NaNs in the accumulators, and
+// values below 2^-110 lose bits of lo below bf16's smallest subnormal, which the
+// split notes. A wave that finds the first in its tile, or results so small that
+// the second counts, computes its outputs again in plain fp32.
+#include <type_traits>
+
+#include "mec_mfma.h"
+
+namespace mec {
+namespace {
+
+struct TileParams {
+    const void* A;  // L or I
+    const void* K;
+    float* O;
+    uint32_t M;     // output pixels
+    int32_t N;      // output channels
+    FastDiv div_v, div_u;      // row p = (n * U + u) * V + v
+    int64_t a_n, a_u, a_v;     // source elements per step of n, u, v
+    int64_t o_n, o_u, o_v, o_off;  // output elements, likewise
+    int32_t nseg, seglen;
+    int64_t xstride;
+    FastDiv div_seg;           // by seglen
+    uint32_t kd;               // nseg * seglen
+    int32_t groups;            // of 8 of its elements
+    int32_t nchunks, n_tiles;
+    uint32_t ntiles;
+};
+
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+
+// 8 fp32 values -> their hi, mid and lo parts, 8 bf16 each: and, subtract and
+// v_perm only, which the matrix cores' instructions hide (6 fit beside each;
+// v_cvt_pk_bf16_f32 takes two slots and v_dot2_f32_bf16 does not overlap them)
+__device__ inline float top(float x) {
+    return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u);
+}
+__device__ inline uint32_t pack_top(float a, float b) {
+    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, a), 0x07060302u);
+}
+// (lost collects the low halves of what lo leaves: nonzero only where bits fall
+// below bf16's smallest subnormal).
+__device__ inline void split8(const float* x, u32x4& h, u32x4& m, u32x4& l, uint32_t& lost) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const float a = x[2 * i], b = x[2 * i + 1];
+        const float ra = a - top(a), rb = b - top(b);
+        const float qa = ra - top(ra), qb = rb - top(rb);
+        h[i] = pack_top(a, b);
+        m[i] = pack_top(ra, rb);
+        l[i] = pack_top(qa, qb);
+        lost |= __builtin_bit_cast(uint32_t, qa) | __builtin_bit_cast(uint32_t, qb);
+    }
+}
+
+// 8 consecutive floats at a 4-byte boundary
+__device__ inline void load8(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, float* x) {
+    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
+    const f32x4 a = __builtin_bit_cast(f32x4, (v4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
+    const f32x4 b = __builtin_bit_cast(f32x4, (v4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16u, 0, 0));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+        x[e] = a[e];
+        x[4 + e] = b[e];
+    }
+}
+
+// BM x BN 32x32 blocks per wave, WM x WN waves. RUN: every run is whole chunks
+// (seglen a multiple of 32), so a chunk's addresses are uniform.
+template <int BM, int BN, int WM, int WN, bool RUN, int MODE>
+struct TileCfg {
+    static constexpr bool kSched = MODE & 1;
+    static constexpr bool kOne = MODE & 2;
+    static constexpr int kVALU = 6;
+    // waves per SIMD that the LDS admits, for the register allocation
+    static constexpr int kWaves = BM * BN == 4 ? (WM * WN == 8 ? 2 : 1) : BM * BN == 2 ? 2 : 3;
+    static constexpr int kBM = BM, kBN = BN, kWM = WM, kWN = WN;
+    static constexpr bool kRun = RUN;
+    static constexpr int KT = 32, G = KT / 8;
+    static constexpr int TM = 32 * BM * WM, TN = 32 * BN * WN;
+    static constexpr int THREADS = 64 * WM * WN;
+    static constexpr int AI = TM * G / THREADS, BI = TN * G / THREADS;
+    static constexpr int ROWB = KT * 2;                  // bytes per LDS row of a plane
+    static constexpr int APL = TM * ROWB, BPL = TN * ROWB;  // bytes per plane
+    static constexpr int STAGE = 3 * (APL + BPL);
+    static_assert(TM * G % THREADS == 0 && TN * G % THREADS == 0 && THREADS % TN == 0 && TN % 64 == 0, "items");
+    static_assert(2 * STAGE + 4 * TM + 16 <= 160 * 1024, "LDS");
+};
+
+// byte offset of granule g (8 elements) of a plane's row: granules permuted so
+// that any 8 or 16 consecutive rows of one granule fall on different banks
+__device__ inline uint32_t swz(uint32_t row, uint32_t g) {
+    return row * 64u + ((g ^ (((row >> 1) ^ (row >> 3)) & 3u)) << 4);
+}
+
+template <class C>
+__global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(TileParams p) {
+    constexpr int BM = C::kBM, BN = C::kBN, G = C::G, TM = C::TM, TN = C::TN;
+    constexpr int AI = C::AI, BI = C::BI, THREADS = C::THREADS;
+    __shared__ __align__(16) char lds[2 * C::STAGE];
+    __shared__ uint32_t lost_s;  // some thread's split left bits out
+    __shared__ __align__(16) uint32_t ooff_s[TM];  // bytes of O from the tile's first image, 2^31 past the last row
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int wm = wave % C::kWM, wn = wave / C::kWM;
+    const uint32_t t = xcd_remap(blockIdx.x, p.ntiles);
+    const uint32_t mt = t / (uint32_t)p.n_tiles, nt = t - mt * (uint32_t)p.n_tiles;
+    const uint32_t m0 = mt * TM;
+    const int n0 = (int)nt * TN;
+
+    // source element of row r of the tile (rows past the last use the last)
+    auto a_base = [&](uint32_t r) -> int64_t {
+        uint32_t row = m0 + r;
+        if (row >= p.M) row = p.M - 1;
+        const uint32_t q = p.div_v.div(row), v = row - q * p.div_v.d;
+        const uint32_t n = p.div_u.div(q), u = q - n * p.div_u.d;
+        return n * p.a_n + u * p.a_u + v * p.a_v;
+    };
+    if (tid == 0) lost_s = 0;  // (ordered by the first barriers)
+    const uint32_t image0 = p.div_u.div(p.div_v.div(m0));
+    for (int r = tid; r < TM; r += THREADS) {
+        const uint32_t row = m0 + r;
+        const uint32_t q = p.div_v.div(row), v = row - q * p.div_v.d;
+        const uint32_t n = p.div_u.div(q), u = q - n * p.div_u.d;
+        ooff_s[r] = row < p.M ? 4u * (uint32_t)((n - image0) * p.o_n + u * p.o_u + v * p.o_v) : 0x80000000u;
+    }
+
+    // staging items: A 8 elements of one row, B 8 k of one column
+    const int ag = tid % G, ar = tid / G;  // A item i: row ar + i * THREADS / G
+    const int bn = tid % TN;               // B item i: group bg + i * THREADS / TN
+    const int bg = __builtin_amdgcn_readfirstlane(tid / TN);
+    // A through a buffer resource based at the tile's first image: a row's offset
+    // there in bytes, plus (RUN) this thread's place in a chunk
+    uint32_t aoff[AI];
+    const char* const Ab = static_cast<const char*>(p.A) + (int64_t)image0 * p.a_n * 4;
+#pragma unroll
+    for (int i = 0; i < AI; ++i)
+        aoff[i] = (uint32_t)(a_base((uint32_t)(ar + i * (THREADS / G))) - (int64_t)image0 * p.a_n) * 4u + (C::kRun ? ag * 32u : 0u);
+    const uint32_t col = (uint32_t)(n0 + bn < p.N ? n0 + bn : p.N - 1);
+    const float* const Kf = static_cast<const float*>(p.K);
+
+    // the registers of a chunk on its way to LDS
+    struct Regs {
+        float a[AI][8], b[BI][8];
+    };
+    // The next chunk's rows of K. Rows past K's end read as 0 by the resource's
+    // range check, so chunks past the last contribute nothing.
+    const char* run_b = reinterpret_cast<const char*>(p.K);
+    int64_t run_left = (int64_t)p.kd * p.N * 4;  // bytes of K from run_b on
+    uint32_t koff[BI][4];  // bytes of this thread's column in 4 rows of K (the next 4 through a second resource)
+#pragma unroll
+    for (int i = 0; i < BI; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            koff[i][e] = 4u * (col + (uint32_t)((bg + i * (THREADS / TN)) * 8 + e) * (uint32_t)p.N);
+    // RUN: the next chunk's position in its run and source offset, uniform
+    int run_r = 0;
+    int64_t run_off = 0;
+    // else: its first group of 8 elements of the reduction
+    uint32_t next_g = 0;
+    auto load = [&](Regs& rg) {
+        if constexpr (C::kRun) {
+            const __amdgpu_buffer_rsrc_t ars =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Ab) + run_off * 4, 0, 0x7fffffff, 0x00027000);
+#pragma unroll
+            for (int i = 0; i < AI; ++i) load8(ars, aoff[i], rg.a[i]);
+        } else {
+            const __amdgpu_buffer_rsrc_t ars =
+                __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(Ab), 0, 0x7fffffff, 0x00027000);
+            uint32_t gi = next_g + (uint32_t)ag;
+            if (gi >= (uint32_t)p.groups) gi = (uint32_t)p.groups - 1;  // meets zeros of B
+            const uint32_t a = p.div_seg.div(gi * 8u), r = gi * 8u - a * (uint32_t)p.seglen;
+            const uint32_t off = (a * (uint32_t)p.xstride + r) * 4u;
+            const uint32_t cnt = (uint32_t)p.seglen - r;  // elements left in the run
+            if (cnt >= 8) {
+#pragma unroll
+                for (int i = 0; i < AI; ++i) load8(ars, aoff[i] + off, rg.a[i]);
+            } else {
+                // the group goes on in the next run (seglen >= 8), or ends past the
+                // reduction: out of the resource's range, read as 0. Masks, not
+                // branches, for the registers' sake.
+                const uint32_t jump = 4u * ((uint32_t)p.xstride - (uint32_t)p.seglen);
+#pragma unroll
+                for (uint32_t e = 0; e < 8; ++e) {
+                    const uint32_t next = (uint32_t)((int32_t)(cnt - 1u - e) >> 31);
+                    const uint32_t past = (uint32_t)((int32_t)(p.kd - 1u - (gi * 8u + e)) >> 31);
+                    const uint32_t oe = off + 4u * e + (jump & next);
+#pragma unroll
+                    for (int i = 0; i < AI; ++i)
+                        rg.a[i][e] = __builtin_bit_cast(
+                            float, __builtin_amdgcn_raw_buffer_load_b32(ars, (aoff[i] + oe) | (past & 0x80000000u), 0, 0));
+                }
+            }
+            next_g += G;
+        }
+        const int left4 = (int)run_left - 16 * p.N;
+        const __amdgpu_buffer_rsrc_t rsrc[2] = {
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(run_b), 0, (int)run_left, 0x00027000),
+            __builtin_amdgcn_make_buffer_rsrc(const_cast<char*>(run_b) + (int64_t)16 * p.N, 0, left4 < 0 ? 0 : left4, 0x00027000)};
+#pragma unroll
+        for (int i = 0; i < BI; ++i)
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                rg.b[i][e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(rsrc[e / 4], koff[i][e % 4], 0, 0));
+        // masks instead of branches, so that the chunk stays one block of code
+        const int64_t kstep = (int64_t)C::KT * 4 * p.N;
+        const int64_t more = ((kstep - run_left) >> 63);                   // ~0 before the last chunk
+        run_b += kstep & more;
+        run_left = (run_left - kstep) & more;
+        if constexpr (C::kRun) {
+            const int64_t wrap = ((int64_t)(run_r + C::KT - p.seglen) >> 63);  // ~0 inside the run
+            run_off += (C::KT + ((p.xstride - p.seglen) & ~wrap)) & more;
+            run_r = (run_r + C::KT) & (int)wrap;
+        }
+    };
+    uint32_t lost = 0;
+    auto stage = [&](const Regs& r, char* __restrict__ to) {
+        char* const ldsA = to;
+        char* const ldsB = to + 3 * C::APL;
+#pragma unroll
+        for (int i = 0; i < AI; ++i) {
+            u32x4 h, m, l;
+            split8(r.a[i], h, m, l, lost);
+            const uint32_t o = swz((uint32_t)(ar + i * (THREADS / G)), (uint32_t)ag);
+            *reinterpret_cast<u32x4*>(ldsA + o) = h;
+            *reinterpret_cast<u32x4*>(ldsA + C::APL + o) = m;
+            *reinterpret_cast<u32x4*>(ldsA + 2 * C::APL + o) = l;
+        }
+#pragma unroll
+        for (int i = 0; i < BI; ++i) {
+            u32x4 h, m, l;
+            split8(r.b[i], h, m, l, lost);
+            const uint32_t o = swz((uint32_t)bn, (uint32_t)(bg + i * (THREADS / TN)));
+            *reinterpret_cast<u32x4*>(ldsB + o) = h;
+            *reinterpret_cast<u32x4*>(ldsB + C::BPL + o) = m;
+            *reinterpret_cast<u32x4*>(ldsB + 2 * C::BPL + o) = l;
+        }
+    };
+
+    floatx16 acc[BM][BN] = {}, low[BM][BN] = {};
+    struct Frags {
+        bf16x8 a[BM][3], b[BN][3];
+    };
+    auto read = [&](Frags& f, const char* __restrict__ from, int kk) {
+        const char* const ldsA = from;
+        const char* const ldsB = from + 3 * C::APL;
+        const uint32_t g = (uint32_t)(2 * kk + (lane >> 5));
+#pragma unroll
+        for (int q = 0; q < 3; ++q) {
+#pragma unroll
+            for (int i = 0; i < BM; ++i)
+                f.a[i][q] = *reinterpret_cast<const bf16x8*>(
+                    ldsA + q * C::APL + swz((uint32_t)((wm * BM + i) * 32 + (lane & 31)), g));
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+                f.b[j][q] = *reinterpret_cast<const bf16x8*>(
+                    ldsB + q * C::BPL + swz((uint32_t)((wn * BN + j) * 32 + (lane & 31)), g));
+        }
+    };
+    auto products = [&](const Frags& f) {
+#define MEC_MM(X, Y, ACC)                                       \
+    _Pragma("unroll") for (int i = 0; i < BM; ++i)              \
+        _Pragma("unroll") for (int j = 0; j < BN; ++j)          \
+            ACC[i][j] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(f.a[i][X], f.b[j][Y], ACC[i][j], 0, 0, 0);
+        MEC_MM(0, 0, acc)
+        MEC_MM(1, 0, low)
+        MEC_MM(0, 1, low)
+        MEC_MM(1, 1, low)
+        MEC_MM(2, 0, low)
+        MEC_MM(0, 2, low)
+#undef MEC_MM
+    };
+
+    // One chunk, in two halves of 16 k. The first half's fragments are in
+    // registers on entry; while its products run, the second half's are read and
+    // the next chunk is split into the other stage. After the barrier the next
+    // chunk's first fragments are read and the chunk after the one already on
+    // its way is requested, under the second half's products. Chunks past the
+    // last are zeros.
+    Frags f0, f1;
+    auto step = [&](Regs& now, const char* __restrict__ cur, char* __restrict__ nxt) {
+        __builtin_amdgcn_sched_barrier(0);
+        read(f1, cur, 1);
+        __builtin_amdgcn_sched_barrier(0);
+        stage(now, nxt);
+        products(f0);
+        if constexpr (C::kSched) {
+#pragma unroll
+            for (int s = 0; s < 6 * BM * BN; ++s) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, C::kVALU, 0);  // VALU
+                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);
+        read(f0, nxt, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load(now);
+        products(f1);
+        if constexpr (C::kSched) {
+#pragma unroll
+            for (int s = 0; s < 6 * BM * BN; ++s) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
+                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global read
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    if constexpr (C::kOne) {
+        Regs r;
+        load(r);
+        stage(r, lds);
+        load(r);
+        __syncthreads();
+        auto one = [&](const char* __restrict__ cur, char* __restrict__ nxt) {
+            read(f0, cur, 0);
+            stage(r, nxt);
+            products(f0);
+            if constexpr (C::kSched) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 3 * (BM + BN), 0);  // LDS read
+#pragma unroll
+                for (int s = 0; s < 6 * BM * BN; ++s) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, C::kVALU, 0);  // VALU
+                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
+                }
+                __builtin_amdgcn_sched_barrier(0);
+            }
+            read(f0, cur, 1);
+            load(r);
+            products(f0);
+            if constexpr (C::kSched) {
+                __builtin_amdgcn_sched_group_barrier(0x100, 3 * (BM + BN), 0);  // LDS read
+#pragma unroll
+                for (int s = 0; s < 6 * BM * BN; ++s) {
+                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
+                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global read
+                }
+            }
+            __syncthreads();
+        };
+        for (int c = 0; c < p.nchunks; c += 2) {
+            one(lds, lds + C::STAGE);
+            one(lds + C::STAGE, lds);
+        }
+    } else {
+    Regs r0, r1;
+    load(r0);
+    load(r1);
+    stage(r0, lds);
+    load(r0);
+    __syncthreads();
+    read(f0, lds, 0);
+    // r1 holds chunk c + 1, r0 chunk c + 2
+    for (int c = 0; c < p.nchunks; c += 2) {
+        step(r1, lds, lds + C::STAGE);
+        step(r0, lds + C::STAGE, lds);
+    }
+    }
+
+    // Values the split does not hold (see the top). Rows and columns past the last
+    // are copies of the last, so all accumulators count.
+    uint32_t most = 0;
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int j = 0; j < BN; ++j)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float x = acc[i][j][v] + low[i][j][v];  // (a bit cast of the vector's element takes element 0)
+                acc[i][j][v] = x;
+                const uint32_t bits = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
+                most = bits > most ? bits : most;
+            }
+    bool bad = most >= 0x7f800000u;
+    if (lost & 0xffffu) lost_s = 1;
+    __syncthreads();
+    if (lost_s) {
+        // what is missing from a result is at most 2^-133 times the sum of the
+        // other operand's values: it counts where that is over 2^-22 of the result
+        float big = 0.0f;
+        for (int r = 0; r < 32 * BM; ++r) {
+            const float* src = static_cast<const float*>(p.A) + a_base((uint32_t)(wm * BM * 32 + r));
+            for (int a = 0; a < p.nseg; ++a)
+                for (int e = lane; e < p.seglen; e += 64) big = __builtin_fmaxf(big, __builtin_fabsf(src[(int64_t)a * p.xstride + e]));
+        }
+        for (int cc = lane; cc < 32 * BN; cc += 64) {
+            const int n = n0 + wn * BN * 32 + cc < p.N ? n0 + wn * BN * 32 + cc : p.N - 1;
+            for (uint32_t k = 0; k < p.kd; ++k) big = __builtin_fmaxf(big, __builtin_fabsf(Kf[(int64_t)k * p.N + n]));
+        }
+        for (int o = 32; o; o >>= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
+        const float bound = big * 0x1p-110f * (float)p.kd;  // 2 * 2^-133 * 2^22
+#pragma unroll
+        for (int i = 0; i < BM; ++i)
+#pragma unroll
+            for (int j = 0; j < BN; ++j)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const float x = __builtin_fabsf(acc[i][j][v]);
+                    bad |= x < bound && x != 0.0f;
+                }
+    }
+    if (__any(bad)) {
+        for (int r = 0; r < 32 * BM; ++r) {
+            const uint32_t oo = ooff_s[wm * BM * 32 + r];
+            if (oo >> 31) continue;
+            float* dst = p.O + p.o_off + (int64_t)image0 * p.o_n + oo / 4;
+            const float* src = static_cast<const float*>(p.A) + a_base((uint32_t)(wm * BM * 32 + r));
+            for (int cc = lane; cc < 32 * BN; cc += 64) {
+                const int n = n0 + wn * BN * 32 + cc;
+                if (n >= p.N) continue;
+                float sum = 0.0f;
+                const float* k = Kf + n;
+                for (int a = 0; a < p.nseg; ++a)
+                    for (int e = 0; e < p.seglen; ++e, k += p.N)
+                        sum = __builtin_fmaf(src[(int64_t)a * p.xstride + e], *k, sum);
+                dst[n] = sum;
+            }
+        }
+        return;
+    }
+    // O through a buffer resource based at the tile's first image: rows past the
+    // last and channels past N have offsets beyond its range and are dropped
+    const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
+        p.O + p.o_off + (int64_t)image0 * p.o_n, 0, 0x40000000, 0x00027000);
+    uint32_t coff[BN];
+#pragma unroll
+    for (int j = 0; j < BN; ++j) {
+        const int n = n0 + (wn * BN + j) * 32 + (lane & 31);
+        coff[j] = n < p.N ? 4u * (uint32_t)n : 0x40000000u;
+    }
+#pragma unroll
+    for (int i = 0; i < BM; ++i)
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const u32x4 ro = *reinterpret_cast<const u32x4*>(&ooff_s[(wm * BM + i) * 32 + acc_row(4 * w, lane)]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+                for (int j = 0; j < BN; ++j) {
+                    const float x = acc[i][j][4 * w + e];
+                    __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), orsrc, ro[e] + coff[j], 0, 2);
+                }
+        }
+}
+
+template <int BM, int BN, int WM, int WN, int SCHED, bool ANY = true>
+hipError_t run_tile(TileParams p, hipStream_t stream) {
+    using CA = TileCfg<BM, BN, WM, WN, true, SCHED>;
+    using CR = TileCfg<BM, BN, WM, WN, false, SCHED>;
+    p.n_tiles = (p.N + CA::TN - 1) / CA::TN;
+    const int64_t ntiles = ((int64_t)p.M + CA::TM - 1) / CA::TM * p.n_tiles;
+    if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
+    p.ntiles = (uint32_t)ntiles;
+    p.nchunks = (p.groups + CA::G - 1) / CA::G;
+    if constexpr (ANY) {
+        if (p.seglen % 32) {
+            hipLaunchKernelGGL(tile_gemm_f32_kernel<CR>, dim3(p.ntiles), dim3(CR::THREADS), 0, stream, p);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL(tile_gemm_f32_kernel<CA>, dim3(p.ntiles), dim3(CA::THREADS), 0, stream, p);
+    return hipGetLastError();
+}
+
+}  // namespace
+
+// Which tile: 0 256x128 (8 waves, one workgroup per compute unit), 1 128x128
+// (one), 2 128x64 (two), 3 64x64 (three). The busiest compute unit takes
+// ceil(tiles / 256) of them, as many at a time as fit; a chunk costs the times
+// below with 1, 2, 3 resident, a tile's start and end the last figure, all in us
+// and measured on this GPU (they give 18 shapes of 20 to 450 us within 7%).
+// Runs that are not whole chunks leave out 128x128, whose gathering loads spill
+// registers (11x11 over 3 channels at batch 32: 226 us, 70 in 256x128).
+int pick_tile(int64_t M, int64_t N, int64_t nchunks, bool run) {
+    struct Opt {
+        int tm, tn, fit;
+        double chunk[3], ends;
+    };
+    constexpr Opt opts[4] = {{256, 128, 1, {1.85, 0, 0}, 10.0},
+                             {128, 128, 1, {1.25, 0, 0}, 4.0},
+                             {128, 64, 2, {0.88, 1.45, 0}, 3.0},
+                             {64, 64, 3, {0.61, 0.85, 1.2}, 2.5}};
+    int best = 0;
+    double best_t = 0.0;
+    for (int i = 0; i < 4; ++i) {
+        if (i == 1 && !run) continue;
+        const Opt& o = opts[i];
+        const int64_t tiles = ((M + o.tm - 1) / o.tm) * ((N + o.tn - 1) / o.tn);
+        const int64_t busiest = (tiles + 255) / 256;
+        const int64_t rounds = busiest / o.fit, rest = busiest % o.fit;
+        double t = (double)rounds * ((double)nchunks * o.chunk[o.fit - 1] + o.ends);
+        if (rest) t += (double)nchunks * o.chunk[rest - 1] + o.ends;
+        if (i == 0 || t < best_t) {
+            best = i;
+            best_t = t;
+        }
+    }
+    return best;
+}
+
+// Taken where its 32-bit offsets hold the shape (rows, K, and the span of O from
+// a tile's first image), except
+// * runs shorter than the groups of 8 they are loaded in,
+// * reductions of one chunk, whose time is the tile's start and end (1x1 over 16
+//   and 32 channels: 24 against 19 us and 13.1 against 12.1 for the plain tiles),
+// * few tiles of a long reduction, where the kernels that split it between two
+//   workgroups fill more of the chip (7x7x512 -> 512 at batch 32, 104 tiles: 86
+//   against 60 us; 14x14x256 at batch 1, 12 tiles: 45 against 28; 36 tiles over 36
+//   chunks 24 against 18; 49 over 18 equal),
+// * the ring kernel's layers (7x7 stride 2 over 3 channels 98 against 83 us, 3x3
+//   over 3 channels 91 against 45; 11x11 over 3 channels to 96, batch 128: 248
+//   against 239 us from L, 226 against 241 from I).
+bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout) {
+    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
+    const int64_t img = layout ? layout->img : s.o_h * s.o_w * s.k_c;
+    const int64_t images = 256 / (s.o_h * s.o_w) + 2;  // that 256 rows can touch
+    const int64_t src = fused ? s.i_h * s.i_w * s.i_c : s.o_w * s.i_h * s.R;  // elements of an image
+    if ((images < s.i_n ? images : s.i_n) * src >= (int64_t(1) << 29)) return false;
+    if (M >= (int64_t(1) << 31) || kd >= (int64_t(1) << 28) || s.k_c >= (int64_t(1) << 28) ||
+        kd * s.k_c >= (int64_t(1) << 29) || (images < s.i_n ? images : s.i_n) * img >= (int64_t(1) << 28))
+        return false;
+    if (kd <= 32 || (fused && s.R < 8)) return false;
+    const bool split_tiles = s.R % 16 == 0 && s.k_c % 4 == 0 &&
+                             ((s.k_h == 3 && s.s_h == 1) || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2));
+    if (split_tiles && kd > 640 && ((M + 63) / 64) * ((s.k_c + 63) / 64) < 112) return false;
+    if (gemm_ring_taken(s, 0, fused, layout)) return false;
+    return true;
+}
+
+hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,
+                            hipStream_t stream, const OutLayout* layout) {
+    TileParams p{};
+    p.A = A;
+    p.K = K;
+    p.O = O;
+    p.M = (uint32_t)(s.i_n * s.o_h * s.o_w);
+    p.N = (int32_t)s.k_c;
+    const OutLayout o = layout ? *layout : OutLayout{s.o_h * s.o_w * s.k_c, s.o_w * s.k_c, s.k_c, 0};
+    p.o_n = o.img;
+    p.o_off = o.off;
+    if (fused) {  // (n, h, w): neighbouring rows read neighbouring pixels
+        p.div_u = FastDiv((uint32_t)s.o_h);
+        p.div_v = FastDiv((uint32_t)s.o_w);
+        p.a_n = s.i_h * s.i_w * s.i_c;
+        p.a_u = s.s_h * s.i_w * s.i_c;
+        p.a_v = s.s_w * s.i_c;
+        p.o_u = o.row;
+        p.o_v = o.col;
+        p.nseg = (int32_t)s.k_h;
+        p.seglen = (int32_t)s.R;
+        p.xstride = s.i_w * s.i_c;
+    } else {  // (n, w, h): neighbouring rows read overlapping windows
+        p.div_u = FastDiv((uint32_t)s.o_w);
+        p.div_v = FastDiv((uint32_t)s.o_h);
+        p.a_n = s.o_w * s.i_h * s.R;
+        p.a_u = s.i_h * s.R;
+        p.a_v = s.s_h * s.R;
+        p.o_u = o.col;
+        p.o_v = o.row;
+        p.nseg = 1;
+        p.seglen = (int32_t)(s.k_h * s.R);
+        p.xstride = 0;
+    }
+    p.kd = (uint32_t)(p.nseg * p.seglen);
+    p.groups = (int32_t)((p.kd + 7) / 8);
+    p.div_seg = FastDiv((uint32_t)p.seglen);
+    switch (pick_tile(p.M, p.N, (p.groups + 3) / 4, p.seglen % 32 == 0)) {
+        case 0: return run_tile<2, 2, 4, 2, 2>(p, stream);
+        case 1: return run_tile<2, 2, 2, 2, 1, false>(p, stream);
+        case 2: return run_tile<1, 2, 4, 1, 1>(p, stream);
+        default: return run_tile<1, 1, 2, 2, 1>(p, stream);
+    }
+}
+
+}  // namespace mec

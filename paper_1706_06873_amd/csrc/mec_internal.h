@@ -122,8 +122,16 @@ bool gemm_ring_usable(const Shape& s, int dtype);
 // the window takes at most two blocks of k-steps: K stays in registers for an
 // item and fills run several blocks ahead
 bool gemm_ring_short(const Shape& s);
+// whether the fixed kernels' dispatch takes the ring (mec_gemm_fixed.hip)
+bool gemm_ring_taken(const Shape& s, int dtype, bool fused, const OutLayout* layout);
 hipError_t launch_gemm_ring(const Shape& s, const void* A, const void* K, float* O, bool fused,
                             hipStream_t stream);
+
+// The slab products on the bf16 matrix cores (mec_gemm_tile.hip): any kernel
+// size, stride and channel count, from L or from I; fp32 as six bf16 products.
+bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout);
+hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,
+                            hipStream_t stream, const OutLayout* layout = nullptr);
 
 // ---------------------------------------------------------------- training passes
 // dL (fp32, L's layout) from G = dloss/dO and K, fp32.
