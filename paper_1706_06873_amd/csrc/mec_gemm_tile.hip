@@ -28,7 +28,7 @@
 // the second counts, computes its outputs again in plain fp32.
 #include <type_traits>
 
-#include "mec_mfma.h"
+#include "mec_split.h"
 
 namespace mec {
 namespace {
@@ -51,45 +51,6 @@ struct TileParams {
     uint32_t ntiles;
 };
 
-typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
-typedef float f32x4 __attribute__((ext_vector_type(4)));
-
-// 8 fp32 values -> their hi, mid and lo parts, 8 bf16 each: and, subtract and
-// v_perm only, which the matrix cores' instructions hide (6 fit beside each;
-// v_cvt_pk_bf16_f32 takes two slots and v_dot2_f32_bf16 does not overlap them)
-__device__ inline float top(float x) {
-    return __builtin_bit_cast(float, __builtin_bit_cast(uint32_t, x) & 0xffff0000u);
-}
-__device__ inline uint32_t pack_top(float a, float b) {
-    return __builtin_amdgcn_perm(__builtin_bit_cast(uint32_t, b), __builtin_bit_cast(uint32_t, a), 0x07060302u);
-}
-// (lost collects the low halves of what lo leaves: nonzero only where bits fall
-// below bf16's smallest subnormal).
-__device__ inline void split8(const float* x, u32x4& h, u32x4& m, u32x4& l, uint32_t& lost) {
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-        const float a = x[2 * i], b = x[2 * i + 1];
-        const float ra = a - top(a), rb = b - top(b);
-        const float qa = ra - top(ra), qb = rb - top(rb);
-        h[i] = pack_top(a, b);
-        m[i] = pack_top(ra, rb);
-        l[i] = pack_top(qa, qb);
-        lost |= __builtin_bit_cast(uint32_t, qa) | __builtin_bit_cast(uint32_t, qb);
-    }
-}
-
-// 8 consecutive floats at a 4-byte boundary
-__device__ inline void load8(__amdgpu_buffer_rsrc_t rsrc, uint32_t off, float* x) {
-    typedef uint32_t v4 __attribute__((ext_vector_type(4)));
-    const f32x4 a = __builtin_bit_cast(f32x4, (v4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off, 0, 0));
-    const f32x4 b = __builtin_bit_cast(f32x4, (v4)__builtin_amdgcn_raw_buffer_load_b128(rsrc, off + 16u, 0, 0));
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-        x[e] = a[e];
-        x[4 + e] = b[e];
-    }
-}
-
 // BM x BN 32x32 blocks per wave, WM x WN waves. RUN: every run is whole chunks
 // (seglen a multiple of 32), so a chunk's addresses are uniform.
 template <int BM, int BN, int WM, int WN, bool RUN, int MODE>
@@ -111,12 +72,6 @@ struct TileCfg {
     static_assert(TM * G % THREADS == 0 && TN * G % THREADS == 0 && THREADS % TN == 0 && TN % 64 == 0, "items");
     static_assert(2 * STAGE + 4 * TM + 16 <= 160 * 1024, "LDS");
 };
-
-// byte offset of granule g (8 elements) of a plane's row: granules permuted so
-// that any 8 or 16 consecutive rows of one granule fall on different banks
-__device__ inline uint32_t swz(uint32_t row, uint32_t g) {
-    return row * 64u + ((g ^ (((row >> 1) ^ (row >> 3)) & 3u)) << 4);
-}
 
 template <class C>
 __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(TileParams p) {

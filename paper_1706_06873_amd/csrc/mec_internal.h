@@ -133,6 +133,11 @@ bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout);
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,
                             hipStream_t stream, const OutLayout* layout = nullptr);
 
+// bf16 products from I with each input value staged once for all taps
+// (mec_gemm_patch.hip): whether it is the one to take, and the launch.
+bool gemm_patch_preferred(const Shape& s, const void* I, const void* K);
+hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
+
 // ---------------------------------------------------------------- training passes
 // dL (fp32, L's layout) from G = dloss/dO and K, fp32.
 bool dgrad_supported(const Shape& s);
