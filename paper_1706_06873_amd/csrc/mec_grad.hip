@@ -29,7 +29,9 @@
 //            turned by 180 degrees and transposed (stride 1: one phase, padding
 //            k-1). pad_grad and phase_kernel form the operands; the forward's
 //            fused slab products write each phase straight into its pixels.
-//  wgrad     a share of the reduction over (pair, output row) on fp32 MFMA: a
+//  wgrad     on the bf16 matrix cores (mec_wgrad_tile.hip) wherever its 32-bit
+//            offsets hold the tensors and rows of L have at least 8 elements; else a
+//            share of the reduction over (pair, output row) on fp32 MFMA: a
 //            workgroup computes a 128 x 64 tile of dK (rows j = a*R + b*i_c + c,
 //            columns m) over the stages in its share, a stage being 16 pairs x
 //            4 output rows, and writes the tile to its own partial buffer;
@@ -874,7 +876,12 @@ hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* p
     p.gvec = s.k_c % 4 == 0 && aligned16(G);
     p.div_ow = FastDiv((uint32_t)s.o_w);
     p.div_R = FastDiv((uint32_t)s.R);
-    if (wgrad_slab_ok(s)) {
+    // the share count within the room the workspace query gave the kernels below
+    if (wgrad_tile_usable(s, fused)) {
+        p.splits = (int32_t)wgrad_tile_splits(s, p.splits);
+        const hipError_t et = launch_wgrad_tile(s, L, G, part, p.splits, stream, fused);
+        if (et != hipSuccess) return et;
+    } else if (wgrad_slab_ok(s)) {
         p.j_tiles = (int32_t)((s.R + kWs - 1) / kWs);
         p.m_tiles = (int32_t)((s.k_c + kWs - 1) / kWs);
         p.ntiles = (uint32_t)((int64_t)p.j_tiles * p.m_tiles * p.splits);

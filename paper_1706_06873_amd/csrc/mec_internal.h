@@ -162,6 +162,12 @@ int64_t wgrad_partial_bytes(const Shape& s);
 // fused: the kernels read the rows of L from I (the L argument is I then).
 hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* part, float* dK,
                         hipStream_t stream, bool fused = false);
+// The products on the bf16 matrix cores (mec_wgrad_tile.hip): whether they take the
+// shape, their share count within `room` shares of partial sums, and the launch.
+bool wgrad_tile_usable(const Shape& s, bool fused);
+int64_t wgrad_tile_splits(const Shape& s, int64_t room);
+hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, float* part, int64_t splits,
+                             hipStream_t stream, bool fused);
 // The static device array that mec_conv2d_wgrad_noalloc uses for the partial
 // sums: its size, and its address on the stream's device (looked up once per
 // device; no allocation).
