@@ -11,7 +11,9 @@
 // and since the lowering copies I into L, dI is the fold of dL: each element
 // of dL added back to the input pixel it was copied from.
 //
-//  dgrad_dl  dL from G and K on fp32 MFMA (v_mfma_f32_32x32x2_f32). A
+//  dgrad_dl  dL from G and K, on the bf16 matrix cores (mec_dgrad_tile.hip) where
+//            that kernel's offsets and tiles serve, else on fp32 MFMA
+//            (v_mfma_f32_32x32x2_f32). There, a
 //            workgroup computes 32 (n, w) pairs x RT consecutive rows r of dL
 //            x 64 columns (b, c). Row r receives G[n, h, w, :] K[a]^T for every
 //            (h, a) with h*s_h + a = r, so the tile stages the hspan rows of G
@@ -717,6 +719,7 @@ bool dgrad_supported(const Shape& s) {
 
 hipError_t launch_dgrad_dl(const Shape& s, const float* G, const float* K, float* dL,
                            hipStream_t stream) {
+    if (dgrad_tile_usable(s)) return launch_dgrad_tile(s, G, K, dL, stream);
     DgradParams p{};
     p.G = G;
     p.K = K;

@@ -143,6 +143,10 @@ hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float
 bool dgrad_supported(const Shape& s);
 hipError_t launch_dgrad_dl(const Shape& s, const float* G, const float* K, float* dL,
                            hipStream_t stream);
+// the same on the bf16 matrix cores (mec_dgrad_tile.hip): whether it is the one to
+// take, and the launch
+bool dgrad_tile_usable(const Shape& s);
+hipError_t launch_dgrad_tile(const Shape& s, const float* G, const float* K, float* dL, hipStream_t stream);
 // dI as s_h*s_w sub-pixel phases, each a stride-1 forward convolution of the
 // zero-padded G with the taps of K that reach it, turned by 180 degrees and
 // transposed (fused slab products, written straight into the phase's pixels
