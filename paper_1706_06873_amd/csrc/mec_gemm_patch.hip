@@ -10,9 +10,9 @@
 // loads (2-byte loads of a transposed stage took 752 instead of 282 us below), and
 // turned by the transposing LDS reads; four taps between barriers, double-buffered.
 // The next chunk's patch waits in registers while the taps of the current one run.
-// 224x224x64 -> 64, 7x7 stride 2, batch 32: 411 us in the plain tiles, 277 here (551
-// TFLOP/s); without the K loads 252, without any staging 228: reads and address
-// work between 16 products per wave and tap, at one wave per SIMD.
+// 224x224x64 -> 64, 7x7 stride 2, batch 32: 402 us in the plain tiles, 240-258 here (590
+// to 635 TFLOP/s). What is left: reads and address work between 16 products per wave
+// and tap, at one wave per SIMD.
 #include "mec_split.h"
 
 namespace mec {
@@ -35,6 +35,7 @@ struct PatchParams {
 // 4 waves of 64 x 64; kItems: patch granules (8 channels of a pixel) per thread at
 // most.
 constexpr int kThreadsP = 256, kTM = 256, kTN = 64, kBM = 2, kBN = 2, kTaps = 4, kItems = 27;
+constexpr int kMaxRows = 512;                   // patch rows at most
 constexpr int kTapBytes = 32 * kTN * 2;         // K of one tap and chunk
 constexpr int kStageBytes = kTaps * kTapBytes;  // one stage of K
 
@@ -43,7 +44,7 @@ __global__ __launch_bounds__(kThreadsP, 1) void patch_gemm_kernel(PatchParams p)
     extern __shared__ __align__(16) char lds[];  // 2 stages of K, then the patch
     __shared__ __align__(16) uint32_t ooff_s[kTM];
     __shared__ uint32_t prow_s[kTM];   // patch row of output row t's first input row
-    __shared__ uint32_t srow_s[kTM];   // I offset (bytes from the tile's first image) of t's first input row
+    __shared__ uint32_t src_s[kMaxRows];  // patch row -> I offset in bytes of its first column, from the tile's first image
     char* const ldsA = lds + 2 * kStageBytes;
 
     const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -68,7 +69,11 @@ __global__ __launch_bounds__(kThreadsP, 1) void patch_gemm_kernel(PatchParams p)
         const int before = k == 0 ? 0 : (first - 1) * p.s_h + p.k_h + (k - 1) * ((p.o_h - 1) * p.s_h + p.k_h);
         const int h_first = k == 0 ? g0 - (int)image0 * p.o_h : 0;
         prow_s[tid] = (uint32_t)(before + (h - h_first) * p.s_h);
-        srow_s[tid] = (uint32_t)(((int64_t)k * p.i_h + (int64_t)h * p.s_h) * p.i_w * p.i_c * ES);
+        // the input rows this output row is the first to bring: all k_h after a new
+        // image, else the last s_h (s_h <= k_h)
+        const int lo = tid == 0 || h == 0 ? 0 : p.k_h - p.s_h;
+        for (int r = lo; r < p.k_h; ++r)
+            src_s[prow_s[tid] + r] = (uint32_t)((k * p.i_h + h * p.s_h + r) * p.i_w) * (uint32_t)(p.i_c * ES);
     }
     __syncthreads();
     for (int m = tid; m < kTM; m += kThreadsP) {
@@ -91,11 +96,7 @@ __global__ __launch_bounds__(kThreadsP, 1) void patch_gemm_kernel(PatchParams p)
         const int pr = (int)p.div_PW.div((uint32_t)q);
         int pc = w0 * p.s_w + q - pr * p.PW;
         if (pc >= p.i_w) pc = p.i_w - 1;  // read by outputs past o_w only
-        // the output row whose input rows hold patch row pr: the last with prow <= pr
-        int lo = 0;
-        for (int step = 128; step; step >>= 1)
-            if (lo + step < th && (int)prow_s[lo + step] <= pr) lo += step;
-        const uint32_t src = srow_s[lo] + (uint32_t)(((pr - (int)prow_s[lo]) * p.i_w + pc) * p.i_c * ES) + ag * 8u * ES;
+        const uint32_t src = q < used ? src_s[pr] + (uint32_t)(pc * p.i_c * ES) + ag * 8u * ES : 0u;
         aoff[i] = q < used ? src : 0x80000000u;  // past the patch: not loaded
     }
     const int64_t from0 = p.i_bytes - (int64_t)image0 * p.i_h * p.i_w * p.i_c * ES;
@@ -304,10 +305,11 @@ PatchTile pick_patch(const Shape& s) {
             const int64_t im = images < s.i_n ? images : s.i_n;
             const int64_t rows = (TH - im) * s.s_h + im * s.k_h;
             const int64_t pixels = rows * ((TW - 1) * s.s_w + s.k_w);
-            if (TH < im || pixels * 4 > (int64_t)kItems * kThreadsP) continue;
-            if (2 * kStageBytes + (pixels + 1) * 64 + 3 * 4 * kTM + 64 > 160 * 1024) continue;
+            if (TH < im || rows > kMaxRows || pixels * 4 > (int64_t)kItems * kThreadsP) continue;
+            if (2 * kStageBytes + (pixels + 1) * 64 + 2 * 4 * kTM + 4 * kMaxRows + 64 > 160 * 1024) continue;
             const double use = (double)(G * s.o_w) / (double)(((G + TH - 1) / TH) * parts * kTM);
             if (use > best.use + 1e-9) best = {(int32_t)TH, (int32_t)TW, (int32_t)pixels, use};
+            break;  // the most rows that fit: a planning loop per call has to stay short
         }
     }
     return best;
@@ -351,11 +353,11 @@ hipError_t run_patch(const Shape& s, const void* I, const void* K, float* O, hip
 // * no tile of its own exists for the kernel with these channels (3x3, 5x5 and 1x1
 //   at stride 1 keep theirs: 3x3 over 64 channels 19 against 46 us), or it is the
 //   7x7 stride 2 one and half the compute units get a workgroup (224x224x64 -> 64,
-//   batch 1, 52 workgroups: 30 against 45 us; batch 4, 196: 69 against 47; batch
-//   32: 402 against 277).
+//   batch 1, 52 workgroups: 30 against 45 us; batch 4, 196: 69 against 43; batch
+//   32: 402 against 258).
 // Against the generic tiles, batch 8 to 64: 3x3 stride 2 over 64 channels 35 -> 26
-// us, over 512 223 -> 90; 3x3 over 100, 90 and 300 channels 89 -> 29, 85 -> 27 and
-// 257 -> 57; 5x5 over 90 186 -> 42; 7x7 stride 2 over 100 at batch 2 406 -> 75.
+// us, over 512 223 -> 90; 3x3 over 100, 90 and 300 channels 89 -> 24, 85 -> 22 and
+// 257 -> 52; 5x5 over 90 186 -> 34; 7x7 stride 2 over 100 at batch 2 406 -> 70.
 bool gemm_patch_preferred(const Shape& s, const void* I, const void* K) {
     if (s.k_h * s.k_w < 2 || s.s_h > s.k_h || s.i_n * s.o_h >= (int64_t(1) << 30)) return false;
     if (s.k_h * s.R * s.k_c >= (int64_t(1) << 30)) return false;

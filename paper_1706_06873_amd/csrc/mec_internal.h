@@ -138,6 +138,11 @@ hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float*
 bool gemm_patch_preferred(const Shape& s, const void* I, const void* K);
 hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
 
+// bf16 products from I over at most 4 input channels (mec_gemm_first.hip): whether
+// they are the ones to take, and the launch.
+bool gemm_first_preferred(const Shape& s, const void* I);
+hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
+
 // ---------------------------------------------------------------- training passes
 // dL (fp32, L's layout) from G = dloss/dO and K, fp32.
 bool dgrad_supported(const Shape& s);
