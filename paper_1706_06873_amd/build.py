@@ -16,7 +16,7 @@ CSRC = os.path.join(PKG, "csrc")
 INCLUDE = os.path.join(REPO, "include")
 LIB = os.path.join(PKG, "libmec.so")
 SOURCES = ["mec_api.cpp", "mec_lower.hip", "mec_im2col.hip", "mec_gemm.hip", "mec_gemm_fixed.hip",
-           "mec_gemm_ring.hip", "mec_gemm_tile.hip", "mec_gemm_patch.hip", "mec_gemm_first.hip",
+           "mec_gemm_ring.hip", "mec_gemm_tile.hip", "mec_gemm_patch.hip", "mec_gemm_first.hip", "mec_gemm_small.hip",
            "mec_grad.hip", "mec_wgrad_tile.hip", "mec_dgrad_tile.hip"]
 ARCH = "gfx950"
 # Per-source flags. The flat-window kernel keeps its accumulators in

@@ -197,9 +197,10 @@ int mec_conv2d(const void* I, const void* K, float* O, void* workspace, size_t w
     if (rc != MEC_OK) return rc;
     // L is there for the caller; where the products from I are the faster ones, they
     // read I, which holds each pixel once (L: k_w / s_w times)
-    if (dtype == MEC_BF16 && mec::gemm_first_preferred(s, I))
+    const bool from_i = dtype == MEC_BF16 && !mec::gemm_small_preferred(s, dtype, false);
+    if (from_i && mec::gemm_first_preferred(s, I))
         return hip_status(mec::launch_gemm_first(s, I, K, O, st), "slab products from the input");
-    if (dtype == MEC_BF16 && mec::gemm_patch_preferred(s, I, K))
+    if (from_i && mec::gemm_patch_preferred(s, I, K))
         return hip_status(mec::launch_gemm_patch(s, I, K, O, st), "slab products from the input");
     return hip_status(mec::launch_gemm(s, workspace, K, O, dtype, false, st), "slab products");
 }

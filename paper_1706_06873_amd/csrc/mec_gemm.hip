@@ -458,6 +458,7 @@ bool gemm_supported(const Shape& s, int dtype, bool fused) {
 
 hipError_t launch_gemm(const Shape& s, const void* A, const void* K, float* O, int dtype,
                        bool fused, hipStream_t stream, const OutLayout* layout) {
+    if (!layout && gemm_small_preferred(s, dtype, fused)) return launch_gemm_small(s, A, K, O, dtype, fused, stream);
     if (fused && dtype != 0 && !layout && gemm_first_preferred(s, A)) return launch_gemm_first(s, A, K, O, stream);
     if (fused && dtype != 0 && !layout && gemm_patch_preferred(s, A, K)) return launch_gemm_patch(s, A, K, O, stream);
     if (dtype == 0 && gemm_tile_usable(s, fused, layout)) return launch_gemm_tile(s, A, K, O, fused, stream, layout);

@@ -143,6 +143,12 @@ hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float
 bool gemm_first_preferred(const Shape& s, const void* I);
 hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
 
+// The products of few outputs and a long reduction (mec_gemm_small.hip), from L or
+// from I: whether they are the ones to take, and the launch.
+bool gemm_small_preferred(const Shape& s, int dtype, bool fused);
+hipError_t launch_gemm_small(const Shape& s, const void* A, const void* K, float* O, int dtype, bool fused,
+                             hipStream_t stream);
+
 // ---------------------------------------------------------------- training passes
 // dL (fp32, L's layout) from G = dloss/dO and K, fp32.
 bool dgrad_supported(const Shape& s);
