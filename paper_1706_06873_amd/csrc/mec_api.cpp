@@ -200,6 +200,8 @@ int mec_conv2d(const void* I, const void* K, float* O, void* workspace, size_t w
     const bool from_i = dtype == MEC_BF16 && !mec::gemm_small_preferred(s, dtype, false);
     if (from_i && mec::gemm_first_preferred(s, I))
         return hip_status(mec::launch_gemm_first(s, I, K, O, st), "slab products from the input");
+    if (dtype == MEC_F32 && !mec::gemm_small_preferred(s, dtype, false) && mec::gemm_tile_from_input(s))
+        return hip_status(mec::launch_gemm_tile(s, I, K, O, true, st), "slab products from the input");
     if (from_i && mec::gemm_patch_preferred(s, I, K))
         return hip_status(mec::launch_gemm_patch(s, I, K, O, st), "slab products from the input");
     return hip_status(mec::launch_gemm(s, workspace, K, O, dtype, false, st), "slab products");

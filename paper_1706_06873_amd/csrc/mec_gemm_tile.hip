@@ -483,6 +483,21 @@ int pick_tile(int64_t M, int64_t N, int64_t nchunks, bool run) {
     return best;
 }
 
+// The ring kernel's tall layers that are faster here from I, against the ring (11x11
+// stride 4 and 9x9 over 3 channels, us, ring / here): 33 to 64 channels always (batch 1
+// 19.6 / 12.8, 32 57.9 / 43.2, 128 181 / 156; 9x9 14.3 / 10.6 to 131 / 116), past 96,
+// which the ring takes in two passes, always (100 channels: 143 / 74, 9x9 103 / 57),
+// between them, where a fourth of a 128-channel tile is empty, with at most 160 tiles
+// (batch 1 25.5 / 12.6, 4 26.8 / 17.4) or full rounds of them (batch 128 245 / 237;
+// 338 tiles in two rounds 66.6 / 71.6, 189 tiles of 9x9 30.5 / 31.8). Up to 32
+// channels the ring leads from batch 16 on (120 / 147 at 128).
+static bool tall_from_input(const Shape& s) {
+    if (s.k_h < 9 || s.R < 24 || s.k_c <= 32 || s.k_c > 128) return false;
+    if (s.k_c <= 64 || s.k_c > 96) return true;
+    const int64_t tiles = (s.i_n * s.o_h * s.o_w + 255) / 256;
+    return tiles <= 160 || 5 * tiles >= 4 * ((tiles + 255) / 256 * 256);
+}
+
 // Taken where its 32-bit offsets hold the shape (rows, K, and the span of O from
 // a tile's first image), except
 // * runs shorter than the groups of 8 they are loaded in,
@@ -493,8 +508,8 @@ int pick_tile(int64_t M, int64_t N, int64_t nchunks, bool run) {
 //   against 60 us; 14x14x256 at batch 1, 12 tiles: 45 against 28; 36 tiles over 36
 //   chunks 24 against 18; 49 over 18 equal),
 // * the ring kernel's layers (7x7 stride 2 over 3 channels 98 against 83 us, 3x3
-//   over 3 channels 91 against 45; 11x11 over 3 channels to 96, batch 128: 248
-//   against 239 us from L, 226 against 241 from I).
+//   over 3 channels 91 against 45; 11x11 over 3 channels to 96, batch 128, from L:
+//   248 against 239), but for the tall kernels below from I.
 bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout) {
     const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
     const int64_t img = layout ? layout->img : s.o_h * s.o_w * s.k_c;
@@ -508,8 +523,12 @@ bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout) {
     const bool split_tiles = s.R % 16 == 0 && s.k_c % 4 == 0 &&
                              ((s.k_h == 3 && s.s_h == 1) || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2));
     if (split_tiles && kd > 640 && ((M + 63) / 64) * ((s.k_c + 63) / 64) < 112) return false;
-    if (gemm_ring_taken(s, 0, fused, layout)) return false;
+    if (gemm_ring_taken(s, 0, fused, layout)) return fused && tall_from_input(s);
     return true;
+}
+
+bool gemm_tile_from_input(const Shape& s) {
+    return gemm_ring_taken(s, 0, false, nullptr) && tall_from_input(s) && gemm_tile_usable(s, true, nullptr);
 }
 
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,

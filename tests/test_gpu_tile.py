@@ -56,6 +56,23 @@ def test_tile_products(orc, dims, algo):
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
 
 
+# tall kernels over 3 channels, which both read I: channel counts at the rule's
+# edges, a batch of less than a tile and one of many
+@pytest.mark.parametrize("k_c", [32, 33, 64, 65, 96, 97, 128, 129])
+@pytest.mark.parametrize("size", [(2, 31, 33, 3, 11, 11), (5, 90, 91, 3, 9, 9)])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_tall_products_from_the_input(orc, size, k_c, algo):
+    dims = size + (k_c, 4, 4)
+    say("tall", dims, algo)
+    I, K = wl.random_case(35, *dims, dist="int")
+    ref = orc.conv2d_direct(I.numpy(), K.numpy(), 4, 4)
+    assert np.array_equal(run(I, K, 4, 4, algo), ref.astype(np.float32))
+    I, K = wl.random_case(36, *dims)
+    ref = orc.conv2d_direct(I.numpy(), K.numpy(), 4, 4).astype(np.float64)
+    got = run(I, K, 4, 4, algo).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
 @pytest.mark.parametrize("shift", [1, 2, 3])
 def test_tile_unaligned_and_guarded(orc, shift):
     dims = (4, 40, 41, 32, 3, 3, 66, 1, 1)
