@@ -3,11 +3,13 @@
 // Tiles of 64 and more rows leave such a shape on a handful of workgroups, each with
 // the whole reduction as a serial chain of staged chunks (1 to 2 us per 32 k). Here a
 // workgroup takes 16 x 16 outputs only and its up to 16 waves share the reduction:
-// each reads its fragments straight from memory into registers, four steps in flight,
+// each reads its fragments straight from memory into registers, up to four steps in flight,
 // with neither staging nor barriers, and the waves' sums are added once, in a fixed
 // order, through LDS. What bounds it is the latency of a wave's few rounds of loads;
 // every value is read once per 16 outputs, which the caches serve. 14x14x256 -> 256 3x3
-// in fp32, one image: 27.4 -> 9.8 us; 7x7x482 -> 276 1x1 in bf16, batch 3: 74 -> 8.3.
+// in fp32, one image: 27.4 -> 8.5 us; 7x7x482 -> 276 1x1 in bf16, batch 3: 74 -> 5.6.
+#include <type_traits>
+
 #include "mec_split.h"
 
 namespace mec {
@@ -28,10 +30,11 @@ struct SmallParams {
     int32_t steps, a_bytes, k_bytes;
 };
 
-constexpr int kSmWaves = 16, kSmUnroll = 4;
+constexpr int kSmWaves = 16;
 
-// VEC: runs are whole groups of a lane's consecutive k, at 4-byte boundaries.
-template <typename T, bool VEC>
+// VEC: runs are whole groups of a lane's consecutive k, at 4-byte boundaries. U: steps
+// in flight.
+template <typename T, bool VEC, int U>
 __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p) {
     constexpr int ES = sizeof(T), EL = 16 / ES, KS = 4 * EL;  // k per lane and step, k per step
     __shared__ float part[kSmWaves][256];
@@ -55,15 +58,15 @@ __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p
     const int begin = wave * p.steps / waves, end = (wave + 1) * p.steps / waves;
     const uint32_t k_end = (uint32_t)end * KS < p.kd ? (uint32_t)end * KS : p.kd;  // this wave's; past it zeros
     floatx4 acc = {};
-    for (int st = begin; st < end; st += kSmUnroll) {
-        u32x4 a[kSmUnroll], b[kSmUnroll];
-        uint32_t x[kSmUnroll][EL], y[kSmUnroll][EL];
+    for (int st = begin; st < end; st += U) {
+        u32x4 a[U], b[U];
+        uint32_t x[U][EL], y[U][EL];
         auto load = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off) -> uint32_t {
             if constexpr (ES == 4) return __builtin_amdgcn_raw_buffer_load_b32(rs, off, 0, 0);
             else return (uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, off, 0, 0);
         };
 #pragma unroll
-        for (int i = 0; i < kSmUnroll; ++i) {
+        for (int i = 0; i < U; ++i) {
             const uint32_t k = (uint32_t)(st + i) * KS + (uint32_t)(lane >> 4) * EL;
             if constexpr (VEC) {
                 const uint32_t seg = p.div_seg.div(k), off = (base + seg * p.xstride + (k - seg * p.div_seg.d)) * ES;
@@ -80,7 +83,7 @@ __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p
             }
         }
 #pragma unroll
-        for (int i = 0; i < kSmUnroll; ++i) {
+        for (int i = 0; i < U; ++i) {
 #pragma unroll
             for (int e = 0; e < 4; ++e) {
                 if constexpr (ES == 4) {
@@ -122,7 +125,7 @@ __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p
 
 // Taken over reductions of at least 64 (below, the time is the call's) where its
 // 32-bit offsets hold the shape, up to so many 16 x 16 tiles as measured, other
-// kernels / here, from I, in us:
+// kernels / here with four steps in flight always, from I, in us:
 // * fp32 to 512 (two workgroups per compute unit): 14x14x256 -> 256 3x3, one image,
 //   144 tiles, 27.4 / 9.8; 7x7x512 -> 512 48 / 16.6; 28x28x128 344 tiles 18.1 / 10.0;
 //   16x16x512 416 tiles 51 / 28; 510 tiles over 864 16.9 / 8.7; past it 732 tiles
@@ -186,10 +189,29 @@ hipError_t launch_gemm_small(const Shape& s, const void* A, const void* K, float
     const bool vec = seglen % el == 0 && even;
     const uint32_t tiles = (uint32_t)(((int64_t)p.M + 15) / 16 * p.n_tiles);
     const int waves = p.steps < kSmWaves ? p.steps : kSmWaves;
-    auto kern = dtype == 0 ? (vec ? small_gemm_kernel<float, true> : small_gemm_kernel<float, false>)
-                           : (vec ? small_gemm_kernel<uint16_t, true> : small_gemm_kernel<uint16_t, false>);
-    hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * waves), 0, stream, p);
-    return hipGetLastError();
+    // Steps in flight: loads past a wave's share cost as much as real ones, so the
+    // count of 4, 3 or fewer that leaves the fewest of them (4 always,
+    // against this: 7x7x482 -> 276 1x1 in bf16, batch 3, 8.3 / 5.6 us, 7x7x512 -> 128,
+    // batch 32, 17.3 / 8.0, 14x14x256 3x3 in fp32 9.8 / 8.5; 8 or 6 at a time 12.4).
+    const int each = (p.steps + waves - 1) / waves;
+    int unroll = 4;
+    for (int u = 3; u >= 1; --u)
+        if ((each + u - 1) / u * u < (each + unroll - 1) / unroll * unroll && (u > 2 || each <= u)) unroll = u;
+    auto launch = [&](auto kern) {
+        hipLaunchKernelGGL(kern, dim3(tiles), dim3(64 * waves), 0, stream, p);
+        return hipGetLastError();
+    };
+    auto pick = [&](auto u) {
+        constexpr int U = decltype(u)::value;
+        if (dtype == 0) return vec ? launch(small_gemm_kernel<float, true, U>) : launch(small_gemm_kernel<float, false, U>);
+        return vec ? launch(small_gemm_kernel<uint16_t, true, U>) : launch(small_gemm_kernel<uint16_t, false, U>);
+    };
+    switch (unroll) {
+        case 1: return pick(std::integral_constant<int, 1>{});
+        case 2: return pick(std::integral_constant<int, 2>{});
+        case 3: return pick(std::integral_constant<int, 3>{});
+        default: return pick(std::integral_constant<int, 4>{});
+    }
 }
 
 }  // namespace mec
