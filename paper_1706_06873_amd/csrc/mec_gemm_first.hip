@@ -225,11 +225,14 @@ __global__ __launch_bounds__(kFtThreads, BN == 2 ? 2 : 1) void first_gemm_kernel
         };
         Frags f0, f1;
         read(f0);
-        for (int s = 0; s < steps; s += 2) {  // (one step past an odd count: zeros of A)
+        // Reads past the last step stay in LDS and are not multiplied: they are of real
+        // weights, and an infinity there times a zero of A would be a NaN.
+        for (int s = 0; s < steps; s += 2) {
             read(f1);
             __builtin_amdgcn_sched_barrier(0);
             products(f0);
             __builtin_amdgcn_sched_barrier(0);
+            if (s + 1 == steps) break;
             read(f0);
             __builtin_amdgcn_sched_barrier(0);
             products(f1);

@@ -68,3 +68,21 @@ def test_first_non_finite(orc):
     got = mec.conv2d(I.to(DEV), K.to(DEV), 1, 1, algo="fused").cpu().numpy()
     assert np.array_equal(np.isnan(got), np.isnan(ref))
     assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
+
+
+# an odd number of steps of two pairs of taps (3x3: 3, 11x11: 33), whose last step
+# stands alone, and an even one (5x5: 8, the last half empty)
+@pytest.mark.parametrize("dims", [(2, 20, 21, 3, 3, 3, 62, 1, 1), (12000, 11, 15, 3, 11, 11, 96, 4, 4),
+                                  (3, 17, 19, 3, 5, 5, 61, 2, 2)])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_first_infinite_weight_in_the_last_tap(orc, dims, algo):
+    print("[case] first infinite weight", dims, algo, flush=True)
+    I, K = wl.random_case(74, *dims, dtype="bf16")
+    I = (I.abs() + 0.25).to(I.dtype)  # no zero meets the infinities
+    K[-1, -1, -1, 0] = float("inf")
+    K[-1, -1, 0, dims[6] - 1] = -float("inf")
+    ref = orc.conv2d_direct(wl.to_oracle_array(I), wl.to_oracle_array(K), dims[7], dims[8])
+    assert np.isinf(ref).any() and not np.isnan(ref).any()
+    got = mec.conv2d(I.to(DEV), K.to(DEV), dims[7], dims[8], algo=algo).cpu().numpy()
+    assert not np.isnan(got).any()
+    assert np.array_equal(got[np.isinf(ref)], ref[np.isinf(ref)].astype(np.float32))
