@@ -200,12 +200,12 @@ __global__ __launch_bounds__(kDtThreads, 2) void dgrad_tile_kernel(DgradTilePara
             const uint32_t bits = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
             most = bits > most ? bits : most;
         }
-    bool bad = most >= 0x7f800000u;
+    const bool bad = most >= 0x7f800000u;
     if (lost & 0xffffu) lost_s = 1;
     __syncthreads();
     float* const out = p.dL + (int64_t)pair0 * p.i_h * p.R;
-    // the plain sum of one element, or the largest value it meets
-    auto plain = [&](uint32_t row, int c, bool largest) {
+    // the plain sum of one element
+    auto plain = [&](uint32_t row, int c) {
         const uint32_t pair = div_y.div(row), n = p.div_ow.div(pair), w = pair - n * p.div_ow.d;
         const int y = (int)(row - pair * Y);
         float sum = 0.0f;
@@ -213,42 +213,16 @@ __global__ __launch_bounds__(kDtThreads, 2) void dgrad_tile_kernel(DgradTilePara
             if ((uint32_t)(y - j) >= (uint32_t)p.o_h) continue;
             const float* gr = p.G + ((int64_t)(n * (uint32_t)p.o_h + (uint32_t)(y - j)) * p.div_ow.d + w) * p.k_c;
             const float* kr = p.K + ((int64_t)(rho + j * p.s_h) * p.R + c) * p.k_c;
-            for (int m = 0; m < p.k_c; ++m)
-                sum = largest ? __builtin_fmaxf(sum, __builtin_fmaxf(__builtin_fabsf(gr[m]), __builtin_fabsf(kr[m])))
-                              : __builtin_fmaf(gr[m], kr[m], sum);
+            for (int m = 0; m < p.k_c; ++m) sum = __builtin_fmaf(gr[m], kr[m], sum);
         }
         return sum;
     };
-    if (lost_s) {
-        // every row of the wave once, and every column
-        float big = 0.0f;
-        for (int k = lane; k < 64; k += 64) {
-            const uint32_t row = m0 + (uint32_t)(wave * 32 + (k & 31));
-            const int c = n0 + k;
-            big = __builtin_fmaxf(big, plain(row < M ? row : M - 1, c < p.R ? c : p.R - 1, true));
-        }
-        // a column's taps may all be cut off for its row: take K's columns whole
-        for (int j = 0; j < taps; ++j)
-            for (int m = 0; m < p.k_c; ++m) {
-                const int c = n0 + lane < p.R ? n0 + lane : p.R - 1;
-                big = __builtin_fmaxf(big, __builtin_fabsf(p.K[((int64_t)(rho + j * p.s_h) * p.R + c) * p.k_c + m]));
-            }
-        for (int o = 32; o; o >>= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
-        const float bound = big * 0x1p-110f * (float)(taps * p.k_c);
-#pragma unroll
-        for (int j = 0; j < 2; ++j)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float x = __builtin_fabsf(acc[j][v]);
-                bad |= x < bound && x != 0.0f;
-            }
-    }
-    if (__any(bad)) {
+    if (lost_s || __any(bad)) {
         for (int k = lane; k < 32 * 64; k += 64) {
             const int r = wave * 32 + (k >> 6), c = n0 + (k & 63);
             const uint32_t oo = ooff_s[r];
             if (oo >> 31 || c >= p.R) continue;
-            out[oo / 4 + c] = plain(m0 + (uint32_t)r, c, false);
+            out[oo / 4 + c] = plain(m0 + (uint32_t)r, c);
         }
         return;
     }

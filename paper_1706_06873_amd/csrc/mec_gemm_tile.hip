@@ -24,8 +24,9 @@
 // Not finite or very small values: an infinity or NaN in a window, and a sum
 // that leaves fp32's range, leave infinities or NaNs in the accumulators, and
 // values below 2^-110 lose bits of lo below bf16's smallest subnormal, which the
-// split notes. A wave that finds the first in its tile, or results so small that
-// the second counts, computes its outputs again in plain fp32.
+// split notes (below 2^-133 nothing is left of them, and a result of 0 may be such a
+// loss). A wave that finds the first in its outputs, and the waves of a workgroup
+// that noted the second, compute their outputs again in plain fp32.
 #include <type_traits>
 
 #include "mec_split.h"
@@ -356,35 +357,10 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
                 const uint32_t bits = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
                 most = bits > most ? bits : most;
             }
-    bool bad = most >= 0x7f800000u;
+    const bool bad = most >= 0x7f800000u;
     if (lost & 0xffffu) lost_s = 1;
     __syncthreads();
-    if (lost_s) {
-        // what is missing from a result is at most 2^-133 times the sum of the
-        // other operand's values: it counts where that is over 2^-22 of the result
-        float big = 0.0f;
-        for (int r = 0; r < 32 * BM; ++r) {
-            const float* src = static_cast<const float*>(p.A) + a_base((uint32_t)(wm * BM * 32 + r));
-            for (int a = 0; a < p.nseg; ++a)
-                for (int e = lane; e < p.seglen; e += 64) big = __builtin_fmaxf(big, __builtin_fabsf(src[(int64_t)a * p.xstride + e]));
-        }
-        for (int cc = lane; cc < 32 * BN; cc += 64) {
-            const int n = n0 + wn * BN * 32 + cc < p.N ? n0 + wn * BN * 32 + cc : p.N - 1;
-            for (uint32_t k = 0; k < p.kd; ++k) big = __builtin_fmaxf(big, __builtin_fabsf(Kf[(int64_t)k * p.N + n]));
-        }
-        for (int o = 32; o; o >>= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
-        const float bound = big * 0x1p-110f * (float)p.kd;  // 2 * 2^-133 * 2^22
-#pragma unroll
-        for (int i = 0; i < BM; ++i)
-#pragma unroll
-            for (int j = 0; j < BN; ++j)
-#pragma unroll
-                for (int v = 0; v < 16; ++v) {
-                    const float x = __builtin_fabsf(acc[i][j][v]);
-                    bad |= x < bound && x != 0.0f;
-                }
-    }
-    if (__any(bad)) {
+    if (lost_s || __any(bad)) {
         for (int r = 0; r < 32 * BM; ++r) {
             const uint32_t oo = ooff_s[wm * BM * 32 + r];
             if (oo >> 31) continue;

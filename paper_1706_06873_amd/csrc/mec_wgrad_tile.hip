@@ -218,31 +218,13 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
             const uint32_t bits = __builtin_bit_cast(uint32_t, x) & 0x7fffffffu;
             most = bits > most ? bits : most;
         }
-    bool bad = most >= 0x7f800000u && m < p.N;
+    const bool bad = most >= 0x7f800000u && m < p.N;
     if (lost & 0xffffu) lost_s = 1;
     __syncthreads();
     const uint32_t p_begin = (uint32_t)c_begin * kPix;
     const uint32_t p_end = (uint32_t)c_end * kPix < p.P ? (uint32_t)c_end * kPix : p.P;
-    if (lost_s) {
-        float big = 0.0f;
-        const int jl = j0 + wj * 64 + lane;
-        const uint32_t sl = p.div_seg.div((uint32_t)jl);
-        for (uint32_t q = p_begin; q < p_end; ++q) {
-            if (jl < p.KD) big = __builtin_fmaxf(big, __builtin_fabsf(p.A[pixel(q) + sl * p.xstride + ((uint32_t)jl - sl * (uint32_t)p.seglen)]));
-            if (m < p.N) big = __builtin_fmaxf(big, __builtin_fabsf(p.G[(int64_t)q * p.N + m]));
-        }
-        for (int o = 32; o; o >>= 1) big = __builtin_fmaxf(big, __shfl_xor(big, o));
-        const float bound = big * 0x1p-110f * (float)(p_end - p_begin);
-#pragma unroll
-        for (int i = 0; i < 2; ++i)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) {
-                const float x = __builtin_fabsf(acc[i][v]);
-                bad |= x < bound && x != 0.0f && m < p.N;
-            }
-    }
     float* const out = p.part + (int64_t)s * p.KD * p.N;
-    if (__any(bad)) {
+    if (lost_s || __any(bad)) {
         for (int k = lane; k < 64 * 32; k += 64) {
             const int jj = j0 + wj * 64 + (k >> 5), mm = m0 + wn * 32 + (k & 31);
             if (jj >= p.KD || mm >= p.N) continue;

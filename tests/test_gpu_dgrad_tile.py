@@ -74,3 +74,16 @@ def test_dgrad_values_the_split_does_not_hold(orc, what):
     assert np.array_equal(got[~fine & ~np.isnan(ref32)], ref32[~fine & ~np.isnan(ref32)])
     ref, got = ref[fine], got[fine].astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# operands below 2^-133, where no bf16 part holds anything, against ordinary ones
+@pytest.mark.parametrize("which", ["kernel", "gradient"])
+def test_dgrad_values_below_every_part(orc, which):
+    dims = (3, 30, 20, 13, 3, 5, 47, 2, 1)
+    print("[case] dgrad values below every part", which, flush=True)
+    K, G = inputs(dims, "u11", 63)
+    K, G = (K * 4e-41, G * 1e6) if which == "kernel" else (K * 1e6, G * 4e-41)
+    ref = orc.mec_dgrad_lowered(G.numpy(), K.numpy(), dims[1], dims[2], dims[7], dims[8]).astype(np.float64)
+    assert np.abs(ref).max() > 1e-36
+    got = run(G, K, dims).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)

@@ -131,3 +131,18 @@ def test_tile_values_the_split_does_not_hold(orc, what, algo):
         assert not fine.all()
     ref, got = ref[fine], got[fine].astype(np.float64)
     assert np.linalg.norm(got - ref) <= tol * np.linalg.norm(ref)
+
+
+# operands below 2^-133, where no bf16 part holds anything, against ordinary ones:
+# their products are ordinary fp32 numbers
+@pytest.mark.parametrize("which", ["input", "kernel"])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_tile_values_below_every_part(orc, which, algo):
+    dims = (3, 40, 40, 20, 3, 3, 70, 1, 1)
+    say("tile values below every part", which, algo)
+    I, K = wl.random_case(37, *dims)
+    I, K = (I * 4e-41, K * 1e6) if which == "input" else (I * 1e6, K * 4e-41)
+    ref = orc.conv2d_direct(I.numpy(), K.numpy(), 1, 1).astype(np.float64)
+    assert np.abs(ref).max() > 1e-36
+    got = run(I, K, 1, 1, algo).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)

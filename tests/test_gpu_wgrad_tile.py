@@ -81,3 +81,16 @@ def test_wgrad_values_the_split_does_not_hold(orc, what):
     assert np.array_equal(got[~fine & ~np.isnan(ref32)], ref32[~fine & ~np.isnan(ref32)])
     ref, got = ref[fine], got[fine].astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# operands below 2^-133, where no bf16 part holds anything, against ordinary ones
+@pytest.mark.parametrize("which", ["input", "gradient"])
+def test_wgrad_values_below_every_part(orc, which):
+    dims = (3, 14, 13, 20, 3, 3, 70, 1, 1)
+    print("[case] wgrad values below every part", which, flush=True)
+    I, G = inputs(dims, "u11", 53)
+    I, G = (I * 4e-41, G * 1e6) if which == "input" else (I * 1e6, G * 4e-41)
+    ref = orc.conv2d_wgrad(I.numpy(), G.numpy(), 3, 3, 1, 1).astype(np.float64)
+    assert np.abs(ref).max() > 1e-36
+    got = both(I, G, dims).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
