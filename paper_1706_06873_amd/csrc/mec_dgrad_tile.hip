@@ -204,27 +204,39 @@ __global__ __launch_bounds__(kDtThreads, 2) void dgrad_tile_kernel(DgradTilePara
     if (lost & 0xffffu) lost_s = 1;
     __syncthreads();
     float* const out = p.dL + (int64_t)pair0 * p.i_h * p.R;
-    // the plain sum of one element
-    auto plain = [&](uint32_t row, int c) {
-        const uint32_t pair = div_y.div(row), n = p.div_ow.div(pair), w = pair - n * p.div_ow.d;
-        const int y = (int)(row - pair * Y);
-        float sum = 0.0f;
-        for (int j = 0; j < taps; ++j) {
-            if ((uint32_t)(y - j) >= (uint32_t)p.o_h) continue;
-            const float* gr = p.G + ((int64_t)(n * (uint32_t)p.o_h + (uint32_t)(y - j)) * p.div_ow.d + w) * p.k_c;
-            const float* kr = p.K + ((int64_t)(rho + j * p.s_h) * p.R + c) * p.k_c;
-            for (int m = 0; m < p.k_c; ++m) sum = __builtin_fmaf(gr[m], kr[m], sum);
-        }
-        return sum;
-    };
     if (lost_s || __any(bad)) {
-        for (int k = lane; k < 32 * 64; k += 64) {
-            const int r = wave * 32 + (k >> 6), c = n0 + (k & 63);
-            const uint32_t oo = ooff_s[r];
-            if (oo >> 31 || c >= p.R) continue;
-            out[oo / 4 + c] = plain(m0 + (uint32_t)r, c);
+        uint32_t row = m0 + (uint32_t)(wave * 32 + (lane & 31));
+        if (row >= M) row = M - 1;
+        const uint32_t pair = div_y.div(row), y = row - pair * Y, n = p.div_ow.div(pair), w = pair - n * p.div_ow.d;
+        const uint32_t go = 4u * ((n * (uint32_t)p.o_h + y) * p.div_ow.d + w) * (uint32_t)p.k_c;
+        // 8 channels from `at` on, zeros past the last or where !on
+        auto fetch = [&](__amdgpu_buffer_rsrc_t rs, uint32_t at, bool on, uint32_t st, float* x) {
+            const int c = (int)(st * 16u) + 8 * (lane >> 5);
+#pragma unroll
+            for (int e = 0; e < 8; ++e)
+                x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                    rs, on && c + e < p.k_c ? at + 4u * (uint32_t)(c + e) : kNone, 0, 0));
+        };
+#pragma unroll
+        for (int j = 0; j < 2; ++j) {
+            const int c = n0 + j * 32 + (lane & 31);
+            const uint32_t co = 4u * ((uint32_t)rho * (uint32_t)p.R + (uint32_t)(c < p.R ? c : p.R - 1)) * (uint32_t)p.k_c;
+            acc[j] = floatx16{};
+            for (uint32_t t = 0; t < (uint32_t)taps; ++t) {
+                floatx16 sum = acc[j];
+                plain_products(
+                    sum, (uint32_t)(p.k_c + 15) / 16u,
+                    [&](uint32_t st, float* x) { fetch(grs, go - t * g_tap, y - t < (uint32_t)p.o_h, st, x); },
+                    [&](uint32_t st, float* x) { fetch(krs, co + t * k_tap, true, st, x); });
+                // rows that this tap does not reach keep their sums: zeros of G may have
+                // met infinities of K
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const uint32_t r = m0 + (uint32_t)(wave * 32 + acc_row(v, lane));
+                    if (r - div_y.div(r) * Y - t < (uint32_t)p.o_h) acc[j][v] = sum[v];
+                }
+            }
         }
-        return;
     }
     const __amdgpu_buffer_rsrc_t ors = buffer(out, 0x40000000);
     uint32_t coff[2];

@@ -26,7 +26,7 @@
 // values below 2^-110 lose bits of lo below bf16's smallest subnormal, which the
 // split notes (below 2^-133 nothing is left of them, and a result of 0 may be such a
 // loss). A wave that finds the first in its outputs, and the waves of a workgroup
-// that noted the second, compute their outputs again in plain fp32.
+// that noted the second, compute their outputs again in plain fp32 (plain_block).
 #include <type_traits>
 
 #include "mec_split.h"
@@ -74,6 +74,40 @@ struct TileCfg {
     static_assert(2 * STAGE + 4 * TM + 16 <= 160 * 1024, "LDS");
 };
 
+// A 32 x 32 block in plain fp32: ro and co are the byte offsets of this lane's row of A,
+// from Ab, and of its column of K. A function of its own and not inlined: inlined, the
+// main loop of the 128 x 64 tile spills 17 to 34 registers.
+__device__ __attribute__((noinline)) floatx16 plain_block(const char* Ab, const char* K, uint32_t ro, uint32_t co, uint32_t kd,
+                                                          uint32_t N, uint32_t seglen, uint32_t xstride, uint64_t div_m,
+                                                          uint32_t div_shift, int lane) {
+    const __amdgpu_buffer_rsrc_t ars = buffer(uniform(Ab), 0x7fffffff), krs = buffer(uniform(K), (int)(uniform(kd) * uniform(N) * 4u));
+    kd = uniform(kd), N = uniform(N);
+    const uint32_t jump = 4u * (xstride - seglen);
+    floatx16 sum = {};
+    plain_products(
+        sum, (kd + 15u) / 16u,
+        [&](uint32_t s, float* x) {  // as load() below
+            const uint32_t k = s * 16u + 8u * (uint32_t)(lane >> 5);
+            const uint32_t a = (uint32_t)(k * div_m >> div_shift), r = k - a * seglen, cnt = seglen - r;
+            const uint32_t off = ro + (a * xstride + r) * 4u;
+            if (cnt >= 8 || k >= kd) {
+                load8(ars, k < kd ? off : 0x80000000u, x);
+            } else {
+#pragma unroll
+                for (uint32_t e = 0; e < 8; ++e)
+                    x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                        ars, k + e < kd ? off + 4u * e + (e >= cnt ? jump : 0u) : 0x80000000u, 0, 0));
+            }
+        },
+        [&](uint32_t s, float* x) {  // rows past kd lie past the resource's end
+            const uint32_t k = s * 16u + 8u * (uint32_t)(lane >> 5);
+#pragma unroll
+            for (uint32_t e = 0; e < 8; ++e)
+                x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(krs, (k + e) * N * 4u + co, 0, 0));
+        });
+    return sum;
+}
+
 template <class C>
 __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(TileParams p) {
     constexpr int BM = C::kBM, BN = C::kBN, G = C::G, TM = C::TM, TN = C::TN;
@@ -118,7 +152,6 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
     for (int i = 0; i < AI; ++i)
         aoff[i] = (uint32_t)(a_base((uint32_t)(ar + i * (THREADS / G))) - (int64_t)image0 * p.a_n) * 4u + (C::kRun ? ag * 32u : 0u);
     const uint32_t col = (uint32_t)(n0 + bn < p.N ? n0 + bn : p.N - 1);
-    const float* const Kf = static_cast<const float*>(p.K);
 
     // the registers of a chunk on its way to LDS
     struct Regs {
@@ -360,29 +393,27 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
     const bool bad = most >= 0x7f800000u;
     if (lost & 0xffffu) lost_s = 1;
     __syncthreads();
-    if (lost_s || __any(bad)) {
-        for (int r = 0; r < 32 * BM; ++r) {
-            const uint32_t oo = ooff_s[wm * BM * 32 + r];
-            if (oo >> 31) continue;
-            float* dst = p.O + p.o_off + (int64_t)image0 * p.o_n + oo / 4;
-            const float* src = static_cast<const float*>(p.A) + a_base((uint32_t)(wm * BM * 32 + r));
-            for (int cc = lane; cc < 32 * BN; cc += 64) {
-                const int n = n0 + wn * BN * 32 + cc;
-                if (n >= p.N) continue;
-                float sum = 0.0f;
-                const float* k = Kf + n;
-                for (int a = 0; a < p.nseg; ++a)
-                    for (int e = 0; e < p.seglen; ++e, k += p.N)
-                        sum = __builtin_fmaf(src[(int64_t)a * p.xstride + e], *k, sum);
-                dst[n] = sum;
-            }
-        }
-        return;
-    }
     // O through a buffer resource based at the tile's first image: rows past the
     // last and channels past N have offsets beyond its range and are dropped
     const __amdgpu_buffer_rsrc_t orsrc = __builtin_amdgcn_make_buffer_rsrc(
         p.O + p.o_off + (int64_t)image0 * p.o_n, 0, 0x40000000, 0x00027000);
+    if (lost_s || __any(bad)) {
+#pragma clang loop unroll(disable)
+        for (int block = 0; block < BM * BN; ++block) {
+            const int i = block / BN, n = n0 + (wn * BN + block % BN) * 32 + (lane & 31);
+            const int64_t row = a_base((uint32_t)((wm * BM + i) * 32 + (lane & 31))) - (int64_t)image0 * p.a_n;
+            const floatx16 sum = plain_block(Ab, static_cast<const char*>(p.K), (uint32_t)row * 4u, 4u * (uint32_t)(n < p.N ? n : p.N - 1),
+                                             p.kd, (uint32_t)p.N, (uint32_t)p.seglen, (uint32_t)p.xstride, p.div_seg.m,
+                                             p.div_seg.shift, lane);
+#pragma unroll
+            for (int v = 0; v < 16; ++v) {
+                const float x = sum[v];
+                const uint32_t at = ooff_s[(wm * BM + i) * 32 + acc_row(v, lane)] + (n < p.N ? 4u * (uint32_t)n : 0x40000000u);
+                __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), orsrc, at, 0, 2);
+            }
+        }
+        return;
+    }
     uint32_t coff[BN];
 #pragma unroll
     for (int j = 0; j < BN; ++j) {

@@ -223,19 +223,33 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
     __syncthreads();
     const uint32_t p_begin = (uint32_t)c_begin * kPix;
     const uint32_t p_end = (uint32_t)c_end * kPix < p.P ? (uint32_t)c_end * kPix : p.P;
-    float* const out = p.part + (int64_t)s * p.KD * p.N;
     if (lost_s || __any(bad)) {
-        for (int k = lane; k < 64 * 32; k += 64) {
-            const int jj = j0 + wj * 64 + (k >> 5), mm = m0 + wn * 32 + (k & 31);
-            if (jj >= p.KD || mm >= p.N) continue;
-            const uint32_t sj = p.div_seg.div((uint32_t)jj);
-            const uint32_t cj = sj * p.xstride + ((uint32_t)jj - sj * (uint32_t)p.seglen);
-            float sum = 0.0f;
-            for (uint32_t q = p_begin; q < p_end; ++q) sum = __builtin_fmaf(p.A[pixel(q) + cj], p.G[(int64_t)q * p.N + mm], sum);
-            out[(int64_t)jj * p.N + mm] = sum;
+        const uint32_t gm = 4u * (uint32_t)(m < p.N ? m : p.N - 1);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const uint32_t jj = (uint32_t)(j0 + wj * 64 + i * 32 + (lane & 31));
+            const uint32_t jc = jj < (uint32_t)p.KD ? jj : (uint32_t)p.KD - 1u, sj = p.div_seg.div(jc);
+            const uint32_t cj = 4u * (sj * p.xstride + (jc - sj * (uint32_t)p.seglen));  // of this lane's row of dK in a window
+            acc[i] = floatx16{};
+            plain_products(
+                acc[i], (p_end - p_begin + 15u) / 16u,
+                [&](uint32_t st, float* x) {
+                    const uint32_t q = p_begin + st * 16u + 8u * (uint32_t)(lane >> 5);
+#pragma unroll
+                    for (uint32_t e = 0; e < 8; ++e)
+                        x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                            ars, q + e < p_end ? pixel(q + e) * 4u + cj : kNone, 0, 0));
+                },
+                [&](uint32_t st, float* x) {
+                    const uint32_t q = p_begin + st * 16u + 8u * (uint32_t)(lane >> 5);
+#pragma unroll
+                    for (uint32_t e = 0; e < 8; ++e)
+                        x[e] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(
+                            grs, q + e < p_end ? (q + e) * (uint32_t)p.N * 4u + gm : kNone, 0, 0));
+                });
         }
-        return;
     }
+    float* const out = p.part + (int64_t)s * p.KD * p.N;
     if (m < p.N) {
 #pragma unroll
         for (int i = 0; i < 2; ++i)

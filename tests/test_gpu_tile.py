@@ -146,3 +146,15 @@ def test_tile_values_below_every_part(orc, which, algo):
     assert np.abs(ref).max() > 1e-36
     got = run(I, K, 1, 1, algo).astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+def test_tile_plain_products_of_the_largest_tile(orc):
+    """Values below 2^-110 throughout: every block of every wave is computed again,
+    runs of whole chunks, tiles of 256 x 128."""
+    dims = (16, 58, 58, 64, 3, 3, 256, 1, 1)
+    say("tile plain products", dims)
+    I, K = wl.random_case(38, *dims)
+    I = I * 1e-35
+    ref = orc.conv2d_direct(I.numpy(), K.numpy(), 1, 1).astype(np.float64)
+    got = run(I, K, 1, 1, "fused").astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
