@@ -9,18 +9,18 @@
 // the window, in chunks of 32.
 //
 // fp32 on bf16 matrix cores. Each fp32 value x is split without loss into three
-// bf16 values, x = hi + mid + lo (hi its upper 8 significant bits, mid the next
-// 8, lo the last 8), and a product is the six bf16 products
+// bf16 values, x = hi + mid + lo (x rounded to 8 significant bits, what that leaves
+// rounded to 8, and the rest; mec_split.h), and a product is the six bf16 products
 //   hi*hi + (hi*mid + mid*hi) + (hi*lo + mid*mid + lo*hi),
-// each exact in fp32. The three left out (mid*lo, lo*mid, lo*lo) are below
-// 2^-22 of the product, 2^-26 on average. v_mfma_f32_32x32x16_bf16 does
+// each exact in fp32. The three left out (mid*lo, lo*mid, lo*lo) come to at most
+// 2^-24 of the product, 2^-28 on average, of either sign. v_mfma_f32_32x32x16_bf16 does
 // 16 times the multiply-adds of v_mfma_f32_32x32x2_f32 in half its cycles per
 // instruction, so six of them still run 2.6 times as many fp32 products. The
 // matrix cores cut sums off at about 2^-24 of the largest addend where the fp32
 // instruction rounds each of its steps, so the five small products go to
 // accumulators of their own, added once at the end. Measured against 64 bits
-// (reductions of 32 to 32768 terms, three distributions): 0.3-0.5 of the fp32
-// instruction's error.
+// (reductions of 32 to 32768 terms; signed, non-negative and constant values): 0.3-0.6
+// of the fp32 instruction's error, and less on constants.
 // Not finite or very small values: an infinity or NaN in a window, and a sum
 // that leaves fp32's range, leave infinities or NaNs in the accumulators, and
 // values below 2^-110 lose bits of lo below bf16's smallest subnormal, which the

@@ -87,3 +87,16 @@ def test_dgrad_values_below_every_part(orc, which):
     assert np.abs(ref).max() > 1e-36
     got = run(G, K, dims).astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# as test_tile_products_left_out: every value the same, up to 48 terms, exact sums of
+# the parts' products
+@pytest.mark.parametrize("bits", [0x3f80ffff, 0x3f807f40, 0x3f808040])
+def test_dgrad_products_left_out(orc, bits):
+    dims = (1, 64, 10, 8, 3, 3, 16, 1, 1)
+    print("[case] dgrad left out", hex(bits), flush=True)
+    x = float(np.array([bits], np.uint32).view(np.float32)[0])
+    G, K = torch.full((1, 62, 8, 16), x), torch.full((3, 3, 8, 16), x)
+    ref = orc.mec_dgrad_lowered(G.numpy(), K.numpy(), 64, 10, 1, 1).astype(np.float64)
+    got = run(G, K, dims).astype(np.float64)
+    assert (np.abs(got - ref) <= 2.0 ** -23 * np.abs(ref)).all()

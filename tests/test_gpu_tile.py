@@ -1,8 +1,8 @@
 """The slab products on the bf16 matrix cores (fp32 as six bf16 products).
 
 Small integers split and sum exactly, so O must match the oracle bit for bit.
-On floats the bar is the split's own: the six products leave out less than
-2^-23 of each product, and the sums are the fp32 accumulators', so O stays
+On floats the bar is the split's own: the six products leave out at most
+2^-24 of each product, and the sums are the fp32 accumulators', so O stays
 within a few fp32 roundings per sum of the 64-bit result, well inside 2e-6.
 """
 import numpy as np
@@ -158,3 +158,37 @@ def test_tile_plain_products_of_the_largest_tile(orc):
     ref = orc.conv2d_direct(I.numpy(), K.numpy(), 1, 1).astype(np.float64)
     got = run(I, K, 1, 1, "fused").astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# small values that the parts hold whole: bf16 subnormals, and values whose middle part
+# is one
+@pytest.mark.parametrize("what", ["subnormal", "subnormal middle part"])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_tile_small_values_held(orc, what, algo):
+    dims = (3, 40, 40, 20, 3, 3, 70, 1, 1)
+    say("tile small values", what, algo)
+    I, K = wl.random_case(39, *dims)
+    if what == "subnormal":
+        I = torch.round(I * 127) * 2.0 ** -133
+    else:
+        I = (1 + torch.round(I.abs() * 8191) / 8192) * 2.0 ** -120
+    K = K * 2.0 ** 40
+    ref = orc.conv2d_direct(I.numpy(), K.numpy(), 1, 1).astype(np.float64)
+    got = run(I, K, 1, 1, algo).astype(np.float64)
+    assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# Every value the same x. The parts' own products and their sums are exact here (288
+# terms of at most 15 bits), so what differs from the 64-bit result is what the six
+# products leave out, below 2^-24 of it, and the rounding of the stored value, 2^-24.
+# x: its last 16 bits set, and the largest middle and last parts there are.
+@pytest.mark.parametrize("bits", [0x3f80ffff, 0x3f807f40, 0x3f808040])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_tile_products_left_out(bits, algo):
+    dims = (5, 30, 31, 32, 3, 3, 65, 1, 1)
+    say("tile left out", hex(bits), algo)
+    x = np.array([bits], np.uint32).view(np.float32)[0]
+    I, K = torch.full(dims[:4], float(x)), torch.full((3, 3, 32, 65), float(x))
+    got = run(I, K, 1, 1, algo).astype(np.float64)
+    ref = 288 * float(x) ** 2
+    assert np.abs(got - ref).max() <= 2.0 ** -23 * ref

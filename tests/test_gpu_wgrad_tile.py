@@ -94,3 +94,15 @@ def test_wgrad_values_below_every_part(orc, which):
     assert np.abs(ref).max() > 1e-36
     got = both(I, G, dims).astype(np.float64)
     assert np.linalg.norm(got - ref) <= 2e-6 * np.linalg.norm(ref)
+
+
+# Every value the same x, 63 terms: as in test_gpu_tile.py's test_tile_products_left_out,
+# and the shares' own sum is rounded once more
+@pytest.mark.parametrize("bits", [0x3f80ffff, 0x3f807f40, 0x3f808040])
+def test_wgrad_products_left_out(bits):
+    dims = (1, 10, 10, 16, 2, 4, 64, 1, 1)
+    print("[case] wgrad left out", hex(bits), flush=True)
+    x = float(np.array([bits], np.uint32).view(np.float32)[0])
+    got = both(torch.full(dims[:4], x), torch.full((1, 9, 7, 64), x), dims).astype(np.float64)
+    ref = 63 * x ** 2
+    assert np.abs(got - ref).max() <= 3 * 2.0 ** -24 * ref
