@@ -195,15 +195,8 @@ int mec_conv2d(const void* I, const void* K, float* O, void* workspace, size_t w
     }
     rc = hip_status(mec::launch_lower(s, I, workspace, (int)es, st), "lowering");
     if (rc != MEC_OK) return rc;
-    // L is there for the caller; where the products from I are the faster ones, they
-    // read I, which holds each pixel once (L: k_w / s_w times)
-    const bool from_i = dtype == MEC_BF16 && !mec::gemm_small_preferred(s, dtype, false);
-    if (from_i && mec::gemm_first_preferred(s, I))
-        return hip_status(mec::launch_gemm_first(s, I, K, O, st), "slab products from the input");
-    if (dtype == MEC_F32 && !mec::gemm_small_preferred(s, dtype, false) && mec::gemm_tile_from_input(s))
-        return hip_status(mec::launch_gemm_tile(s, I, K, O, true, st), "slab products from the input");
-    if (from_i && mec::gemm_patch_preferred(s, I, K))
-        return hip_status(mec::launch_gemm_patch(s, I, K, O, st), "slab products from the input");
+    if (mec::gemm_from_input(s, I, K, dtype))
+        return hip_status(mec::launch_gemm(s, I, K, O, dtype, true, st), "slab products from the input");
     return hip_status(mec::launch_gemm(s, workspace, K, O, dtype, false, st), "slab products");
 }
 
@@ -322,6 +315,87 @@ int mec_conv2d_wgrad(const void* I, const float* G, float* dK, void* workspace,
     // the products read L's rows straight from I: no lowering pass
     return hip_status(mec::launch_wgrad(s, static_cast<const float*>(I), G, part, dK, st, true),
                       "wgrad products from I");
+}
+
+// ---------------------------------------------------------------- for the tests
+// What mec_internal.h declares for them: the kernel that a call takes, and a call of one
+// kernel on any shape that it holds.
+
+int mec_internal_gemm_route(const void* I, const void* K, int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c,
+                            int s_h, int s_w, int dtype, int algo, int* from_input) {
+    mec::Shape s;
+    const int rc = make_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w);
+    if (rc != MEC_OK) return rc;
+    if (!valid_dtype(dtype) || (algo != MEC_ALGO_LOWERED && algo != MEC_ALGO_FUSED)) return MEC_ERR_INVALID_ARG;
+    const bool fused = algo == MEC_ALGO_FUSED || mec::gemm_from_input(s, I, K, dtype);
+    if (from_input) *from_input = fused;
+    return (int)mec::gemm_route(s, I, K, dtype, fused, nullptr);
+}
+
+int mec_internal_gemm(int kernel, const void* A, const void* K, float* O, int i_n, int i_h, int i_w, int i_c, int k_h,
+                      int k_w, int k_c, int s_h, int s_w, int dtype, int fused, void* stream) {
+    mec::Shape s;
+    const int rc = make_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w);
+    if (rc != MEC_OK) return rc;
+    if (!valid_dtype(dtype) || !A || !K || !O) return MEC_ERR_INVALID_ARG;
+    const int64_t es = elem_bytes(dtype);
+    if (!aligned(A, es) || !aligned(K, es) || !aligned(O, 4)) return MEC_ERR_ALIGNMENT;
+    bool holds = false;
+    switch ((mec::GemmKernel)kernel) {
+        case mec::GemmKernel::kSmall: holds = mec::gemm_small_holds(s, dtype, fused); break;
+        case mec::GemmKernel::kFirst: holds = dtype == MEC_BF16 && fused && mec::gemm_first_holds(s, A); break;
+        case mec::GemmKernel::kPatch: holds = dtype == MEC_BF16 && fused && mec::gemm_patch_holds(s, A, K); break;
+        case mec::GemmKernel::kTile: holds = dtype == MEC_F32 && mec::gemm_tile_holds(s, fused, nullptr); break;
+        case mec::GemmKernel::kFixed: holds = mec::gemm_supported(s, dtype, fused); break;
+        default: return MEC_ERR_INVALID_ARG;
+    }
+    if (!holds) return MEC_ERR_UNSUPPORTED;
+    clear_stale_error();
+    return hip_status(mec::launch_gemm_by((mec::GemmKernel)kernel, s, A, K, O, dtype, fused, (hipStream_t)stream),
+                      "one kernel's slab products");
+}
+
+int mec_internal_wgrad(int kernel, const void* A, const float* G, float* dK, void* workspace, size_t workspace_bytes,
+                       int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w, int fused,
+                       void* stream) {
+    mec::Shape s;
+    const int rc = grad_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w, MEC_F32);
+    if (rc != MEC_OK) return rc;
+    if (!A || !G || !dK) return MEC_ERR_INVALID_ARG;
+    if (!aligned(A, 4) || !aligned(G, 4) || !aligned(dK, 4) || !aligned(workspace, 4)) return MEC_ERR_ALIGNMENT;
+    if (!mec::wgrad_supported(s)) return MEC_ERR_UNSUPPORTED;
+    if (!workspace || (uint64_t)workspace_bytes < (uint64_t)mec::wgrad_partial_bytes(s)) return MEC_ERR_WORKSPACE;
+    switch ((mec::WgradKernel)kernel) {
+        case mec::WgradKernel::kTile: if (!mec::wgrad_tile_holds(s, fused)) return MEC_ERR_UNSUPPORTED; break;
+        case mec::WgradKernel::kSlab: if (!mec::wgrad_slab_ok(s)) return MEC_ERR_UNSUPPORTED; break;
+        case mec::WgradKernel::kGeneral: if (mec::wgrad_slab_ok(s)) return MEC_ERR_UNSUPPORTED; break;
+        default: return MEC_ERR_INVALID_ARG;
+    }
+    clear_stale_error();
+    return hip_status(mec::launch_wgrad_by((mec::WgradKernel)kernel, s, static_cast<const float*>(A), G,
+                                           static_cast<float*>(workspace), dK, (hipStream_t)stream, fused),
+                      "one kernel's wgrad products");
+}
+
+int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w, int fused) {
+    mec::Shape s;
+    const int rc = grad_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w, MEC_F32);
+    if (rc != MEC_OK) return rc;
+    return (int)mec::wgrad_route(s, fused);
+}
+
+int mec_internal_dgrad_gemm(int tile, const float* G, const float* K, float* dL, int i_n, int i_h, int i_w, int i_c,
+                            int k_h, int k_w, int k_c, int s_h, int s_w, void* stream) {
+    mec::Shape s;
+    const int rc = grad_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w, MEC_F32);
+    if (rc != MEC_OK) return rc;
+    if (!G || !K || !dL) return MEC_ERR_INVALID_ARG;
+    if (!aligned(G, 4) || !aligned(K, 4) || !aligned(dL, 4)) return MEC_ERR_ALIGNMENT;
+    if (tile ? !mec::dgrad_tile_holds(s) : !mec::dgrad_supported(s)) return MEC_ERR_UNSUPPORTED;
+    clear_stale_error();
+    return hip_status(tile ? mec::launch_dgrad_tile(s, G, K, dL, (hipStream_t)stream)
+                           : mec::launch_dgrad_fp32(s, G, K, dL, (hipStream_t)stream),
+                      "one kernel's dgrad products");
 }
 
 int64_t mec_noalloc_scratch_bytes(void) { return mec::kNoAllocScratchBytes; }

@@ -260,14 +260,19 @@ __global__ __launch_bounds__(kDtThreads, 2) void dgrad_tile_kernel(DgradTilePara
 
 }  // namespace
 
-// Taken where its 32-bit offsets hold G, K and a tile's rows of dL, the strides are
-// at most kMaxClasses, and there is work for tiles of 128 x 64 over chunks of 32
-// channels.
-bool dgrad_tile_usable(const Shape& s) {
+// Its 32-bit offsets hold G, K and a tile's rows of dL, and the strides are at most
+// kMaxClasses.
+bool dgrad_tile_holds(const Shape& s) {
     const int64_t lim = int64_t(1) << 29;
     if (s.s_h > kMaxClasses || s.i_n * s.o_h * s.o_w * s.k_c >= lim || s.k_h * s.R * s.k_c >= lim) return false;
     const int64_t Y = s.i_h / s.s_h > 0 ? s.i_h / s.s_h : 1;
-    if ((128 / Y + 2) * s.i_h * s.R >= (int64_t(1) << 28) || s.pairs * s.i_h >= (int64_t(1) << 30)) return false;
+    return (128 / Y + 2) * s.i_h * s.R < (int64_t(1) << 28) && s.pairs * s.i_h < (int64_t(1) << 30);
+}
+
+// Taken where it holds the shape and there is work for tiles of 128 x 64 over chunks of
+// 32 channels.
+bool dgrad_tile_preferred(const Shape& s) {
+    if (!dgrad_tile_holds(s)) return false;
     return s.k_c >= 16 && s.R >= 24 && s.pairs * s.i_h >= 512;
 }
 

@@ -456,12 +456,36 @@ bool gemm_supported(const Shape& s, int dtype, bool fused) {
     return dispatch<false>(s, nullptr, nullptr, nullptr, dtype, nullptr, true) == hipSuccess;
 }
 
+GemmKernel gemm_route(const Shape& s, const void* A, const void* K, int dtype, bool fused, const OutLayout* layout) {
+    if (!layout && gemm_small_preferred(s, dtype, fused)) return GemmKernel::kSmall;
+    if (fused && dtype != 0 && !layout && gemm_first_preferred(s, A)) return GemmKernel::kFirst;
+    if (fused && dtype != 0 && !layout && gemm_patch_preferred(s, A, K)) return GemmKernel::kPatch;
+    if (dtype == 0 && gemm_tile_preferred(s, fused, layout)) return GemmKernel::kTile;
+    return GemmKernel::kFixed;
+}
+
+// With L in the workspace the products read I, which holds each pixel once (L: k_w / s_w
+// times), where a kernel that reads I is the faster one.
+bool gemm_from_input(const Shape& s, const void* I, const void* K, int dtype) {
+    if (gemm_small_preferred(s, dtype, false)) return false;
+    if (dtype == 0) return gemm_tile_from_input(s);
+    return gemm_first_preferred(s, I) || gemm_patch_preferred(s, I, K);
+}
+
 hipError_t launch_gemm(const Shape& s, const void* A, const void* K, float* O, int dtype,
                        bool fused, hipStream_t stream, const OutLayout* layout) {
-    if (!layout && gemm_small_preferred(s, dtype, fused)) return launch_gemm_small(s, A, K, O, dtype, fused, stream);
-    if (fused && dtype != 0 && !layout && gemm_first_preferred(s, A)) return launch_gemm_first(s, A, K, O, stream);
-    if (fused && dtype != 0 && !layout && gemm_patch_preferred(s, A, K)) return launch_gemm_patch(s, A, K, O, stream);
-    if (dtype == 0 && gemm_tile_usable(s, fused, layout)) return launch_gemm_tile(s, A, K, O, fused, stream, layout);
+    return launch_gemm_by(gemm_route(s, A, K, dtype, fused, layout), s, A, K, O, dtype, fused, stream, layout);
+}
+
+hipError_t launch_gemm_by(GemmKernel kernel, const Shape& s, const void* A, const void* K, float* O, int dtype,
+                          bool fused, hipStream_t stream, const OutLayout* layout) {
+    switch (kernel) {
+        case GemmKernel::kSmall: return launch_gemm_small(s, A, K, O, dtype, fused, stream);
+        case GemmKernel::kFirst: return launch_gemm_first(s, A, K, O, stream);
+        case GemmKernel::kPatch: return launch_gemm_patch(s, A, K, O, stream);
+        case GemmKernel::kTile: return launch_gemm_tile(s, A, K, O, fused, stream, layout);
+        case GemmKernel::kFixed: break;
+    }
     // kernels specialised for this kernel height and stride first; only they
     // take a strided output layout
     const hipError_t e = launch_gemm_fixed(s, A, K, O, dtype, fused, stream, false, layout);

@@ -302,14 +302,18 @@ int first_tn(const Shape& s) { return s.k_c <= 64 ? 64 : 96; }
 // stride 4 -> 96 batch 32 83 -> 37 us, batch 1 (49 tiles) 13 against 24; 7x7 stride 2 ->
 // 64 batch 32 81 -> 31; 224x224x3 3x3 -> 64 batch 32 100 -> 81 (its 404 MB of output at
 // 5 TB/s), batch 16 54 -> 44, batch 1 12.3 and 12.7.
-bool gemm_first_preferred(const Shape& s, const void* I) {
+bool gemm_first_holds(const Shape& s, const void* I) {
     if (s.i_c > 4 || s.k_h * s.k_w < 2 || s.s_h > s.k_h || ((uintptr_t)I & 3u)) return false;
     if (s.i_n * s.o_h >= (int64_t(1) << 30) || s.k_h * s.R * s.k_c >= (int64_t(1) << 30)) return false;
     const int64_t images = 256 / s.o_h + 2;
     const int64_t im = images < s.i_n ? images : s.i_n;
     if (im * s.o_h * s.o_w * s.k_c >= (int64_t(1) << 28) || im * s.i_h * s.i_w * s.i_c >= (int64_t(1) << 29)) return false;
+    return pick_first(s, first_tn(s)).TH != 0;
+}
+
+bool gemm_first_preferred(const Shape& s, const void* I) {
+    if (!gemm_first_holds(s, I)) return false;
     const FirstTile t = pick_first(s, first_tn(s));
-    if (!t.TH) return false;
     const int64_t tiles = ((s.i_n * s.o_h + t.TH - 1) / t.TH) * ((s.o_w + t.TW - 1) / t.TW);
     return first_k_bytes(s, first_tn(s)) <= 32 * 1024 || tiles >= 256;
 }

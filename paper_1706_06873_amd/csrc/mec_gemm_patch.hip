@@ -358,16 +358,20 @@ hipError_t run_patch(const Shape& s, const void* I, const void* K, float* O, hip
 // Against the generic tiles, batch 8 to 64: 3x3 stride 2 over 64 channels 35 -> 26
 // us, over 512 223 -> 90; 3x3 over 100, 90 and 300 channels 89 -> 24, 85 -> 22 and
 // 257 -> 52; 5x5 over 90 186 -> 34; 7x7 stride 2 over 100 at batch 2 406 -> 70.
-bool gemm_patch_preferred(const Shape& s, const void* I, const void* K) {
+bool gemm_patch_holds(const Shape& s, const void* I, const void* K) {
     if (s.k_h * s.k_w < 2 || s.s_h > s.k_h || s.i_n * s.o_h >= (int64_t(1) << 30)) return false;
     if (s.k_h * s.R * s.k_c >= (int64_t(1) << 30)) return false;
     const int64_t images = 256 / s.o_h + 2;
     const int64_t im = images < s.i_n ? images : s.i_n;
     if (im * s.o_h * s.o_w * s.k_c >= (int64_t(1) << 28) || im * s.i_h * s.i_w * s.i_c >= (int64_t(1) << 30)) return false;
     if (s.i_c % 2 || s.k_c % 2 || ((uintptr_t)I & 3u) || ((uintptr_t)K & 3u)) return false;
+    return pick_patch(s).TH != 0;
+}
+
+bool gemm_patch_preferred(const Shape& s, const void* I, const void* K) {
+    if (!gemm_patch_holds(s, I, K)) return false;
     if (5 * s.i_c * s.k_c < 2 * ((s.i_c + 31) / 32 * 32) * ((s.k_c + 63) / 64 * 64)) return false;
     const PatchTile t = pick_patch(s);
-    if (!t.TH) return false;
     if (launch_gemm_fixed(s, I, K, nullptr, 1, true, nullptr, true) != hipSuccess) return true;
     const int64_t tiles = ((s.i_n * s.o_h + t.TH - 1) / t.TH) * ((s.o_w + t.TW - 1) / t.TW) * ((s.k_c + kTN - 1) / kTN);
     return s.k_h == 7 && s.s_h == 2 && tiles >= 128;

@@ -123,8 +123,15 @@ __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p
 
 }  // namespace
 
-// Taken over reductions of at least 64 (below, the time is the call's) where its
-// 32-bit offsets hold the shape, up to so many 16 x 16 tiles as measured, other
+// Its 32-bit offsets hold the shape.
+bool gemm_small_holds(const Shape& s, int dtype, bool fused) {
+    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R, es = dtype == 0 ? 4 : 2, lim = int64_t(1) << 31;
+    const int64_t src = fused ? s.i_n * s.i_h * s.i_w * s.i_c : s.i_n * s.o_w * s.i_h * s.R;
+    return src * es < lim && kd * s.k_c * es < lim && M < (int64_t(1) << 26);
+}
+
+// Taken over reductions of at least 64 (below, the time is the call's) where it holds
+// the shape, up to so many 16 x 16 tiles as measured, other
 // kernels / here with four steps in flight always, from I, in us:
 // * fp32 to 512 (two workgroups per compute unit): 14x14x256 -> 256 3x3, one image,
 //   144 tiles, 27.4 / 9.8; 7x7x512 -> 512 48 / 16.6; 28x28x128 344 tiles 18.1 / 10.0;
@@ -137,9 +144,8 @@ __global__ __launch_bounds__(64 * kSmWaves) void small_gemm_kernel(SmallParams p
 // * 1x1 kernels in bf16 to 1024: 7x7x2048 -> 512, batch 8, 800 tiles, 78 / 21; 784
 //   tiles over 64 9.1 / 4.4.
 bool gemm_small_preferred(const Shape& s, int dtype, bool fused) {
-    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R, es = dtype == 0 ? 4 : 2, lim = int64_t(1) << 31;
-    const int64_t src = fused ? s.i_n * s.i_h * s.i_w * s.i_c : s.i_n * s.o_w * s.i_h * s.R;
-    if (src * es >= lim || kd * s.k_c * es >= lim || M >= (int64_t(1) << 26)) return false;
+    if (!gemm_small_holds(s, dtype, fused)) return false;
+    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
     const int64_t tiles = ((M + 15) / 16) * ((s.k_c + 15) / 16);
     if (kd < 64) return false;
     return tiles <= (dtype == 0 ? (kd < 128 ? 256 : 512) : s.k_h == 1 ? 1024 : 256);

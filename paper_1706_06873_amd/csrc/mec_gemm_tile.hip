@@ -505,9 +505,21 @@ static bool tall_from_input(const Shape& s) {
     return tiles <= 160 || 5 * tiles >= 4 * ((tiles + 255) / 256 * 256);
 }
 
-// Taken where its 32-bit offsets hold the shape (rows, K, and the span of O from
-// a tile's first image), except
-// * runs shorter than the groups of 8 they are loaded in,
+// Its 32-bit offsets hold the shape: rows, K, and the span of O from a tile's first
+// image. Runs are at least the groups of 8 they are loaded in.
+bool gemm_tile_holds(const Shape& s, bool fused, const OutLayout* layout) {
+    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
+    const int64_t img = layout ? layout->img : s.o_h * s.o_w * s.k_c;
+    const int64_t images = 256 / (s.o_h * s.o_w) + 2;  // that 256 rows can touch
+    const int64_t src = fused ? s.i_h * s.i_w * s.i_c : s.o_w * s.i_h * s.R;  // elements of an image
+    if ((images < s.i_n ? images : s.i_n) * src >= (int64_t(1) << 29)) return false;
+    if (M >= (int64_t(1) << 31) || kd >= (int64_t(1) << 28) || s.k_c >= (int64_t(1) << 28) ||
+        kd * s.k_c >= (int64_t(1) << 29) || (images < s.i_n ? images : s.i_n) * img >= (int64_t(1) << 28))
+        return false;
+    return (fused ? s.R : kd) >= 8;
+}
+
+// Taken where it holds the shape, except for
 // * reductions of one chunk, whose time is the tile's start and end (1x1 over 16
 //   and 32 channels: 24 against 19 us and 13.1 against 12.1 for the plain tiles),
 // * few tiles of a long reduction, where the kernels that split it between two
@@ -517,16 +529,10 @@ static bool tall_from_input(const Shape& s) {
 // * the ring kernel's layers (7x7 stride 2 over 3 channels 98 against 83 us, 3x3
 //   over 3 channels 91 against 45; 11x11 over 3 channels to 96, batch 128, from L:
 //   248 against 239), but for the tall kernels below from I.
-bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout) {
+bool gemm_tile_preferred(const Shape& s, bool fused, const OutLayout* layout) {
+    if (!gemm_tile_holds(s, fused, layout)) return false;
     const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
-    const int64_t img = layout ? layout->img : s.o_h * s.o_w * s.k_c;
-    const int64_t images = 256 / (s.o_h * s.o_w) + 2;  // that 256 rows can touch
-    const int64_t src = fused ? s.i_h * s.i_w * s.i_c : s.o_w * s.i_h * s.R;  // elements of an image
-    if ((images < s.i_n ? images : s.i_n) * src >= (int64_t(1) << 29)) return false;
-    if (M >= (int64_t(1) << 31) || kd >= (int64_t(1) << 28) || s.k_c >= (int64_t(1) << 28) ||
-        kd * s.k_c >= (int64_t(1) << 29) || (images < s.i_n ? images : s.i_n) * img >= (int64_t(1) << 28))
-        return false;
-    if (kd <= 32 || (fused && s.R < 8)) return false;
+    if (kd <= 32) return false;
     const bool split_tiles = s.R % 16 == 0 && s.k_c % 4 == 0 &&
                              ((s.k_h == 3 && s.s_h == 1) || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2));
     if (split_tiles && kd > 640 && ((M + 63) / 64) * ((s.k_c + 63) / 64) < 112) return false;
@@ -535,7 +541,7 @@ bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout) {
 }
 
 bool gemm_tile_from_input(const Shape& s) {
-    return gemm_ring_taken(s, 0, false, nullptr) && tall_from_input(s) && gemm_tile_usable(s, true, nullptr);
+    return gemm_ring_taken(s, 0, false, nullptr) && tall_from_input(s) && gemm_tile_preferred(s, true, nullptr);
 }
 
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,

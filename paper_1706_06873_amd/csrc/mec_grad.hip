@@ -719,7 +719,11 @@ bool dgrad_supported(const Shape& s) {
 
 hipError_t launch_dgrad_dl(const Shape& s, const float* G, const float* K, float* dL,
                            hipStream_t stream) {
-    if (dgrad_tile_usable(s)) return launch_dgrad_tile(s, G, K, dL, stream);
+    if (dgrad_tile_preferred(s)) return launch_dgrad_tile(s, G, K, dL, stream);
+    return launch_dgrad_fp32(s, G, K, dL, stream);
+}
+
+hipError_t launch_dgrad_fp32(const Shape& s, const float* G, const float* K, float* dL, hipStream_t stream) {
     DgradParams p{};
     p.G = G;
     p.K = K;
@@ -854,8 +858,17 @@ bool wgrad_supported(const Shape& s) {
            wgrad_tiles(s) * wgrad_splits(s) < (int64_t(1) << 31);
 }
 
+WgradKernel wgrad_route(const Shape& s, bool fused) {
+    return wgrad_tile_holds(s, fused) ? WgradKernel::kTile : wgrad_slab_ok(s) ? WgradKernel::kSlab : WgradKernel::kGeneral;
+}
+
 hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* part, float* dK,
                         hipStream_t stream, bool fused) {
+    return launch_wgrad_by(wgrad_route(s, fused), s, L, G, part, dK, stream, fused);
+}
+
+hipError_t launch_wgrad_by(WgradKernel kernel, const Shape& s, const float* L, const float* G, float* part, float* dK,
+                           hipStream_t stream, bool fused) {
     WgradParams p{};
     p.L = L;
     p.fused = fused;
@@ -880,11 +893,11 @@ hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* p
     p.div_ow = FastDiv((uint32_t)s.o_w);
     p.div_R = FastDiv((uint32_t)s.R);
     // the share count within the room the workspace query gave the kernels below
-    if (wgrad_tile_usable(s, fused)) {
+    if (kernel == WgradKernel::kTile) {
         p.splits = (int32_t)wgrad_tile_splits(s, p.splits);
         const hipError_t et = launch_wgrad_tile(s, L, G, part, p.splits, stream, fused);
         if (et != hipSuccess) return et;
-    } else if (wgrad_slab_ok(s)) {
+    } else if (kernel == WgradKernel::kSlab) {
         p.j_tiles = (int32_t)((s.R + kWs - 1) / kWs);
         p.m_tiles = (int32_t)((s.k_c + kWs - 1) / kWs);
         p.ntiles = (uint32_t)((int64_t)p.j_tiles * p.m_tiles * p.splits);

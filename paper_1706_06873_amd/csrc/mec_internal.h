@@ -2,6 +2,7 @@
 // kernels (mec_lower.hip, mec_gemm.hip). Not part of the public ABI.
 #pragma once
 
+#include <stddef.h>
 #include <stdint.h>
 
 #include <hip/hip_runtime_api.h>
@@ -85,13 +86,25 @@ struct GemmParams {
 
 struct OutLayout;
 
+// The kernels that compute the slab products, in the order in which they are tried:
+// mec_gemm_small.hip, mec_gemm_first.hip, mec_gemm_patch.hip, mec_gemm_tile.hip, and the
+// others (mec_gemm_fixed.hip, which may hand over to mec_gemm_ring.hip, and
+// mec_gemm.hip), and which of them a call takes.
+enum class GemmKernel { kSmall = 0, kFirst = 1, kPatch = 2, kTile = 3, kFixed = 4 };
+GemmKernel gemm_route(const Shape& s, const void* A, const void* K, int dtype, bool fused, const OutLayout* layout);
+// whether mec_conv2d's products should read I although L is there
+bool gemm_from_input(const Shape& s, const void* I, const void* K, int dtype);
+
 // Enqueue the slab products. fused selects the I-sourced variant.
 // Returns hipErrorInvalidValue when the shape exceeds the kernels' on-chip
 // limits (see gemm_supported), else the launch status. A strided output
-// layout (fp32 only) is taken by the fixed kernels alone: hipErrorNotSupported
-// when none of them matches.
+// layout (fp32 only) is taken by the tile and the fixed kernels alone:
+// hipErrorNotSupported when none of them matches.
 hipError_t launch_gemm(const Shape& s, const void* A, const void* K, float* O, int dtype,
                        bool fused, hipStream_t stream, const OutLayout* layout = nullptr);
+// the same by one of them, which has to hold the shape
+hipError_t launch_gemm_by(GemmKernel kernel, const Shape& s, const void* A, const void* K, float* O, int dtype,
+                          bool fused, hipStream_t stream, const OutLayout* layout = nullptr);
 
 // Whether the slab-product kernels can run this shape (LDS limits), from L
 // (fused = false) or staged from I (fused = true): from L, every kernel height
@@ -129,24 +142,27 @@ hipError_t launch_gemm_ring(const Shape& s, const void* A, const void* K, float*
 
 // The slab products on the bf16 matrix cores (mec_gemm_tile.hip): any kernel
 // size, stride and channel count, from L or from I; fp32 as six bf16 products.
-bool gemm_tile_usable(const Shape& s, bool fused, const OutLayout* layout);
+bool gemm_tile_holds(const Shape& s, bool fused, const OutLayout* layout);
+bool gemm_tile_preferred(const Shape& s, bool fused, const OutLayout* layout);
 // whether it should read I although L is there
 bool gemm_tile_from_input(const Shape& s);
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,
                             hipStream_t stream, const OutLayout* layout = nullptr);
 
 // bf16 products from I with each input value staged once for all taps
-// (mec_gemm_patch.hip): whether it is the one to take, and the launch.
+// (mec_gemm_patch.hip): whether it holds the shape and is the one to take, and the launch.
+bool gemm_patch_holds(const Shape& s, const void* I, const void* K);
 bool gemm_patch_preferred(const Shape& s, const void* I, const void* K);
 hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
 
-// bf16 products from I over at most 4 input channels (mec_gemm_first.hip): whether
-// they are the ones to take, and the launch.
+// bf16 products from I over at most 4 input channels (mec_gemm_first.hip): likewise.
+bool gemm_first_holds(const Shape& s, const void* I);
 bool gemm_first_preferred(const Shape& s, const void* I);
 hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream);
 
 // The products of few outputs and a long reduction (mec_gemm_small.hip), from L or
-// from I: whether they are the ones to take, and the launch.
+// from I: likewise.
+bool gemm_small_holds(const Shape& s, int dtype, bool fused);
 bool gemm_small_preferred(const Shape& s, int dtype, bool fused);
 hipError_t launch_gemm_small(const Shape& s, const void* A, const void* K, float* O, int dtype, bool fused,
                              hipStream_t stream);
@@ -156,9 +172,12 @@ hipError_t launch_gemm_small(const Shape& s, const void* A, const void* K, float
 bool dgrad_supported(const Shape& s);
 hipError_t launch_dgrad_dl(const Shape& s, const float* G, const float* K, float* dL,
                            hipStream_t stream);
-// the same on the bf16 matrix cores (mec_dgrad_tile.hip): whether it is the one to
-// take, and the launch
-bool dgrad_tile_usable(const Shape& s);
+// the same by the fp32 kernels
+hipError_t launch_dgrad_fp32(const Shape& s, const float* G, const float* K, float* dL, hipStream_t stream);
+// the same on the bf16 matrix cores (mec_dgrad_tile.hip): whether it holds the shape and
+// is the one to take, and the launch
+bool dgrad_tile_holds(const Shape& s);
+bool dgrad_tile_preferred(const Shape& s);
 hipError_t launch_dgrad_tile(const Shape& s, const float* G, const float* K, float* dL, hipStream_t stream);
 // dI as s_h*s_w sub-pixel phases, each a stride-1 forward convolution of the
 // zero-padded G with the taps of K that reach it, turned by 180 degrees and
@@ -179,9 +198,15 @@ int64_t wgrad_partial_bytes(const Shape& s);
 // fused: the kernels read the rows of L from I (the L argument is I then).
 hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* part, float* dK,
                         hipStream_t stream, bool fused = false);
-// The products on the bf16 matrix cores (mec_wgrad_tile.hip): whether they take the
+// the kernels of its products, and which of them a call takes
+enum class WgradKernel { kTile = 0, kSlab = 1, kGeneral = 2 };
+WgradKernel wgrad_route(const Shape& s, bool fused);
+bool wgrad_slab_ok(const Shape& s);
+hipError_t launch_wgrad_by(WgradKernel kernel, const Shape& s, const float* L, const float* G, float* part, float* dK,
+                           hipStream_t stream, bool fused);
+// The products on the bf16 matrix cores (mec_wgrad_tile.hip): whether they hold the
 // shape, their share count within `room` shares of partial sums, and the launch.
-bool wgrad_tile_usable(const Shape& s, bool fused);
+bool wgrad_tile_holds(const Shape& s, bool fused);
 int64_t wgrad_tile_splits(const Shape& s, int64_t room);
 hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, float* part, int64_t splits,
                              hipStream_t stream, bool fused);
@@ -192,6 +217,23 @@ constexpr int64_t kNoAllocScratchBytes = int64_t(64) << 20;
 hipError_t noalloc_scratch(hipStream_t stream, void** ptr);
 
 }  // namespace mec
+
+// For the tests, which load the library through the public header's ABI; not part of it.
+// The kernel (GemmKernel, WgradKernel) that mec_conv2d and the weight gradient take, and
+// *from_input whether the products read I; nothing is launched and no pointer read.
+extern "C" int mec_internal_gemm_route(const void* I, const void* K, int i_n, int i_h, int i_w, int i_c, int k_h, int k_w,
+                                       int k_c, int s_h, int s_w, int dtype, int algo, int* from_input);
+extern "C" int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w,
+                                        int fused);
+// The products by one kernel, on any shape that it holds (else MEC_ERR_UNSUPPORTED); A is
+// I where fused, else L; dgrad: tile or the fp32 kernels.
+extern "C" int mec_internal_gemm(int kernel, const void* A, const void* K, float* O, int i_n, int i_h, int i_w, int i_c,
+                                 int k_h, int k_w, int k_c, int s_h, int s_w, int dtype, int fused, void* stream);
+extern "C" int mec_internal_wgrad(int kernel, const void* A, const float* G, float* dK, void* workspace,
+                                  size_t workspace_bytes, int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c,
+                                  int s_h, int s_w, int fused, void* stream);
+extern "C" int mec_internal_dgrad_gemm(int tile, const float* G, const float* K, float* dL, int i_n, int i_h, int i_w,
+                                       int i_c, int k_h, int k_w, int k_c, int s_h, int s_w, void* stream);
 
 #if defined(__HIP__)
 namespace mec {

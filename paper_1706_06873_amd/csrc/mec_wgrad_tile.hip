@@ -263,7 +263,7 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
 
 }  // namespace
 
-bool wgrad_tile_usable(const Shape& s, bool fused) {
+bool wgrad_tile_holds(const Shape& s, bool fused) {
     const int64_t src = fused ? s.i_n * s.i_h * s.i_w * s.i_c : s.i_n * s.o_w * s.i_h * s.R;
     if (src * 4 >= (int64_t(1) << 31) || s.i_n * s.o_h * s.o_w * s.k_c * 4 >= (int64_t(1) << 31)) return false;
     return s.R >= 8;

@@ -1,0 +1,70 @@
+"""Calls of one kernel of the library, past the choice that its entry points make
+(mec_internal.h), and that choice itself."""
+import ctypes
+
+import torch
+
+import paper_1706_06873_amd as mec
+
+SMALL, FIRST, PATCH, TILE, FIXED = range(5)           # GemmKernel
+WGRAD_TILE, WGRAD_SLAB, WGRAD_GENERAL = range(3)      # WgradKernel
+UNSUPPORTED = -5
+ALIGNED = 0x100000
+
+_i, _vp = ctypes.c_int, ctypes.c_void_p
+_lib = mec.lib
+_lib.mec_internal_gemm_route.argtypes = [_vp, _vp] + [_i] * 11 + [ctypes.POINTER(_i)]
+_lib.mec_internal_wgrad_route.argtypes = [_i] * 10
+_lib.mec_internal_gemm.argtypes = [_i, _vp, _vp, _vp] + [_i] * 11 + [_vp]
+_lib.mec_internal_wgrad.argtypes = [_i, _vp, _vp, _vp, _vp, ctypes.c_size_t] + [_i] * 10 + [_vp]
+_lib.mec_internal_dgrad_gemm.argtypes = [_i, _vp, _vp, _vp] + [_i] * 9 + [_vp]
+
+
+def route(dims, dtype="f32", algo="lowered", I=ALIGNED, K=ALIGNED):
+    """(the kernel that conv2d's products take, whether they read I)."""
+    from_input = _i(0)
+    code = mec.F32 if dtype == "f32" else mec.BF16
+    kind = mec.LOWERED if algo == "lowered" else mec.FUSED
+    r = _lib.mec_internal_gemm_route(I, K, *dims, code, kind, ctypes.byref(from_input))
+    assert r >= 0, (dims, r)
+    return r, bool(from_input.value)
+
+
+def wgrad_route(dims, fused):
+    r = _lib.mec_internal_wgrad_route(*dims, int(fused))
+    assert r >= 0, (dims, r)
+    return r
+
+
+def gemm(kernel, A, K, dims, fused, O=None):
+    """O by one kernel from A (I if fused, else L), or None where it does not hold the
+    shape."""
+    i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w = dims
+    o_h, o_w = mec.output_dims(i_h, i_w, k_h, k_w, s_h, s_w)
+    if O is None:
+        O = torch.full((i_n, o_h, o_w, k_c), 7.0, device=A.device)
+    r = _lib.mec_internal_gemm(kernel, A.data_ptr(), K.data_ptr(), O.data_ptr(), *dims,
+                               mec.BF16 if A.dtype == torch.bfloat16 else mec.F32, int(fused),
+                               torch.cuda.current_stream().cuda_stream)
+    assert r in (0, UNSUPPORTED), (dims, r)
+    return O if r == 0 else None
+
+
+def wgrad(kernel, A, G, dims, fused):
+    i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w = dims
+    dK = torch.full((k_h, k_w, i_c, k_c), 7.0, device=A.device)
+    ws = torch.empty(mec.grad_workspace_bytes(*dims, grad_pass=mec.GRAD_KERNEL), dtype=torch.uint8, device=A.device)
+    r = _lib.mec_internal_wgrad(kernel, A.data_ptr(), G.data_ptr(), dK.data_ptr(), ws.data_ptr(), ws.numel(), *dims,
+                                int(fused), torch.cuda.current_stream().cuda_stream)
+    assert r in (0, UNSUPPORTED), (dims, r)
+    return dK if r == 0 else None
+
+
+def dgrad_gemm(tile, G, K, dims):
+    i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w = dims
+    o_w = mec.output_dims(i_h, i_w, k_h, k_w, s_h, s_w)[1]
+    dL = torch.full((i_n, o_w, i_h, k_w, i_c), 7.0, device=G.device)
+    r = _lib.mec_internal_dgrad_gemm(int(tile), G.data_ptr(), K.data_ptr(), dL.data_ptr(), *dims,
+                                     torch.cuda.current_stream().cuda_stream)
+    assert r in (0, UNSUPPORTED), (dims, r)
+    return dL if r == 0 else None

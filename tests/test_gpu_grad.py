@@ -3,6 +3,10 @@
 Bars as for the forward pass: with small-integer inputs every partial sum is
 exact in fp32, so dL, dI and dK must match the oracle bit for bit; with
 uniform random inputs they must be within relative L2 error 1e-5.
+
+Notes beside the shapes name the fp32 kernels; the entry points give most of these
+shapes to the kernels on the bf16 matrix cores, and test_gpu_kernels.py calls the fp32
+kernels themselves on them.
 """
 import numpy as np
 import pytest

@@ -5,6 +5,10 @@ bf16 inputs within 1e-5 of the oracle fed the same bf16 values (the GPU
 accumulates in fp32) and within 1e-2 of the oracle fed the fp32 values before
 rounding. With small-integer inputs every partial sum is exact in fp32, so O
 must then match bit for bit.
+
+Notes beside the shapes name the fixed and generic kernels' tiles. The entry points
+give many of these shapes to other kernels; test_gpu_kernels.py calls those kernels
+themselves on them.
 """
 import numpy as np
 import pytest
