@@ -366,7 +366,7 @@ int mec_internal_wgrad(int kernel, const void* A, const float* G, float* dK, voi
     if (!mec::wgrad_supported(s)) return MEC_ERR_UNSUPPORTED;
     if (!workspace || (uint64_t)workspace_bytes < (uint64_t)mec::wgrad_partial_bytes(s)) return MEC_ERR_WORKSPACE;
     switch ((mec::WgradKernel)kernel) {
-        case mec::WgradKernel::kTile: if (!mec::wgrad_tile_holds(s, fused)) return MEC_ERR_UNSUPPORTED; break;
+        case mec::WgradKernel::kTile: if (!mec::wgrad_tile_holds(s)) return MEC_ERR_UNSUPPORTED; break;
         case mec::WgradKernel::kSlab: if (!mec::wgrad_slab_ok(s)) return MEC_ERR_UNSUPPORTED; break;
         case mec::WgradKernel::kGeneral: if (mec::wgrad_slab_ok(s)) return MEC_ERR_UNSUPPORTED; break;
         default: return MEC_ERR_INVALID_ARG;
@@ -377,11 +377,11 @@ int mec_internal_wgrad(int kernel, const void* A, const float* G, float* dK, voi
                       "one kernel's wgrad products");
 }
 
-int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w, int fused) {
+int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w) {
     mec::Shape s;
     const int rc = grad_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w, MEC_F32);
     if (rc != MEC_OK) return rc;
-    return (int)mec::wgrad_route(s, fused);
+    return (int)mec::wgrad_route(s);
 }
 
 int mec_internal_dgrad_gemm(int tile, const float* G, const float* K, float* dL, int i_n, int i_h, int i_w, int i_c,

@@ -858,13 +858,13 @@ bool wgrad_supported(const Shape& s) {
            wgrad_tiles(s) * wgrad_splits(s) < (int64_t(1) << 31);
 }
 
-WgradKernel wgrad_route(const Shape& s, bool fused) {
-    return wgrad_tile_holds(s, fused) ? WgradKernel::kTile : wgrad_slab_ok(s) ? WgradKernel::kSlab : WgradKernel::kGeneral;
+WgradKernel wgrad_route(const Shape& s) {
+    return wgrad_tile_holds(s) ? WgradKernel::kTile : wgrad_slab_ok(s) ? WgradKernel::kSlab : WgradKernel::kGeneral;
 }
 
 hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* part, float* dK,
                         hipStream_t stream, bool fused) {
-    return launch_wgrad_by(wgrad_route(s, fused), s, L, G, part, dK, stream, fused);
+    return launch_wgrad_by(wgrad_route(s), s, L, G, part, dK, stream, fused);
 }
 
 hipError_t launch_wgrad_by(WgradKernel kernel, const Shape& s, const float* L, const float* G, float* part, float* dK,

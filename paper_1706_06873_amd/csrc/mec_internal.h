@@ -200,13 +200,13 @@ hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* p
                         hipStream_t stream, bool fused = false);
 // the kernels of its products, and which of them a call takes
 enum class WgradKernel { kTile = 0, kSlab = 1, kGeneral = 2 };
-WgradKernel wgrad_route(const Shape& s, bool fused);
+WgradKernel wgrad_route(const Shape& s);
 bool wgrad_slab_ok(const Shape& s);
 hipError_t launch_wgrad_by(WgradKernel kernel, const Shape& s, const float* L, const float* G, float* part, float* dK,
                            hipStream_t stream, bool fused);
 // The products on the bf16 matrix cores (mec_wgrad_tile.hip): whether they hold the
 // shape, their share count within `room` shares of partial sums, and the launch.
-bool wgrad_tile_holds(const Shape& s, bool fused);
+bool wgrad_tile_holds(const Shape& s);
 int64_t wgrad_tile_splits(const Shape& s, int64_t room);
 hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, float* part, int64_t splits,
                              hipStream_t stream, bool fused);
@@ -223,8 +223,7 @@ hipError_t noalloc_scratch(hipStream_t stream, void** ptr);
 // *from_input whether the products read I; nothing is launched and no pointer read.
 extern "C" int mec_internal_gemm_route(const void* I, const void* K, int i_n, int i_h, int i_w, int i_c, int k_h, int k_w,
                                        int k_c, int s_h, int s_w, int dtype, int algo, int* from_input);
-extern "C" int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w,
-                                        int fused);
+extern "C" int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w);
 // The products by one kernel, on any shape that it holds (else MEC_ERR_UNSUPPORTED); A is
 // I where fused, else L; dgrad: tile or the fp32 kernels.
 extern "C" int mec_internal_gemm(int kernel, const void* A, const void* K, float* O, int i_n, int i_h, int i_w, int i_c,

@@ -29,7 +29,8 @@ struct WgradTileParams {
     uint32_t xstride;
     uint32_t a_n, a_h, a_w; // source elements per step of n, h, w
     FastDiv div_ow, div_oh, div_seg;
-    int32_t a_bytes, g_bytes;
+    int64_t a_bytes;
+    int32_t g_bytes;
     int32_t j_tiles, m_tiles, splits, chunks;  // chunks of 32 pixels in all
     uint32_t ntiles;
 };
@@ -55,11 +56,12 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
     const int c_begin = (int)((int64_t)s * p.chunks / p.splits), c_end = (int)((int64_t)(s + 1) * p.chunks / p.splits);
     if (tid == 0) lost_s = 0;
 
-    // source element of pixel p's window
+    // source element of pixel p's window, from the share's first image on
+    const uint32_t image0 = p.div_oh.div(p.div_ow.div((uint32_t)c_begin * kPix));
     auto pixel = [&](uint32_t q) -> uint32_t {
         const uint32_t r = p.div_ow.div(q), w = q - r * p.div_ow.d;
         const uint32_t n = p.div_oh.div(r), h = r - n * p.div_oh.d;
-        return n * p.a_n + h * p.a_h + w * p.a_w;
+        return (n - image0) * p.a_n + h * p.a_h + w * p.a_w;
     };
     // staging: A pixels tid / 16 and + 16, columns 8 (tid % 16)..; G pixel tid / 8,
     // columns 8 (tid % 8)..
@@ -70,7 +72,9 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
     const uint32_t jcol = (seg * p.xstride + r0) * 4u;
     const uint32_t run = (uint32_t)p.seglen - r0;        // elements left in the run
     const uint32_t jump = 4u * (p.xstride - (uint32_t)p.seglen);
-    const __amdgpu_buffer_rsrc_t ars = buffer(p.A, p.a_bytes), grs = buffer(p.G, p.g_bytes);
+    const int64_t a_first = (int64_t)image0 * p.a_n, a_left = p.a_bytes - a_first * 4;
+    const __amdgpu_buffer_rsrc_t ars = buffer(p.A + a_first, a_left > 0x7fffffff ? 0x7fffffff : (int)a_left),
+                                 grs = buffer(p.G, p.g_bytes);
     constexpr uint32_t kNone = 0x80000000u;  // past any range: read as 0
     const uint32_t none = j < (uint32_t)p.KD ? 0u : kNone;
     // the offsets of chunk c's pixels, worked out once by one wave
@@ -263,10 +267,15 @@ __global__ __launch_bounds__(kWgThreads, 2) void wgrad_tile_kernel(WgradTilePara
 
 }  // namespace
 
-bool wgrad_tile_holds(const Shape& s, bool fused) {
-    const int64_t src = fused ? s.i_n * s.i_h * s.i_w * s.i_c : s.i_n * s.o_w * s.i_h * s.R;
-    if (src * 4 >= (int64_t(1) << 31) || s.i_n * s.o_h * s.o_w * s.k_c * 4 >= (int64_t(1) << 31)) return false;
-    return s.R >= 8;
+// Its 32-bit offsets hold the shape: G, and the images that a share's windows lie in. From
+// L and from I alike, since dK is the same bit for bit from either.
+bool wgrad_tile_holds(const Shape& s) {
+    const int64_t lim = int64_t(1) << 31, pixels = s.i_n * s.o_h * s.o_w;
+    if (s.R < 8 || pixels * s.k_c * 4 >= lim || s.i_n * s.i_h * s.i_w * s.i_c * 4 >= lim) return false;
+    const int64_t image = s.o_w * s.i_h * s.R * 4;
+    if (s.i_n * image < lim) return true;
+    const int64_t chunks = (pixels + kPix - 1) / kPix, splits = wgrad_tile_splits(s, wgrad_splits(s));
+    return ((chunks / splits + 1) * kPix / (s.o_h * s.o_w) + 2) * image < lim;
 }
 
 // Shares: the count, at most the partial sums' room, that minimises the busiest
@@ -305,7 +314,7 @@ hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, flo
         p.a_n = (uint32_t)(s.i_h * s.i_w * s.i_c);
         p.a_h = (uint32_t)(s.s_h * s.i_w * s.i_c);
         p.a_w = (uint32_t)(s.s_w * s.i_c);
-        p.a_bytes = (int32_t)(s.i_n * s.i_h * s.i_w * s.i_c * 4);
+        p.a_bytes = s.i_n * s.i_h * s.i_w * s.i_c * 4;
     } else {
         p.nseg = 1;
         p.seglen = p.KD;
@@ -313,7 +322,7 @@ hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, flo
         p.a_n = (uint32_t)(s.o_w * s.i_h * s.R);
         p.a_h = (uint32_t)(s.s_h * s.R);
         p.a_w = (uint32_t)(s.i_h * s.R);
-        p.a_bytes = (int32_t)(s.i_n * s.o_w * s.i_h * s.R * 4);
+        p.a_bytes = s.i_n * s.o_w * s.i_h * s.R * 4;
     }
     p.g_bytes = (int32_t)(s.i_n * s.o_h * s.o_w * s.k_c * 4);
     p.div_ow = FastDiv((uint32_t)s.o_w);

@@ -14,7 +14,7 @@ ALIGNED = 0x100000
 _i, _vp = ctypes.c_int, ctypes.c_void_p
 _lib = mec.lib
 _lib.mec_internal_gemm_route.argtypes = [_vp, _vp] + [_i] * 11 + [ctypes.POINTER(_i)]
-_lib.mec_internal_wgrad_route.argtypes = [_i] * 10
+_lib.mec_internal_wgrad_route.argtypes = [_i] * 9
 _lib.mec_internal_gemm.argtypes = [_i, _vp, _vp, _vp] + [_i] * 11 + [_vp]
 _lib.mec_internal_wgrad.argtypes = [_i, _vp, _vp, _vp, _vp, ctypes.c_size_t] + [_i] * 10 + [_vp]
 _lib.mec_internal_dgrad_gemm.argtypes = [_i, _vp, _vp, _vp] + [_i] * 9 + [_vp]
@@ -30,8 +30,8 @@ def route(dims, dtype="f32", algo="lowered", I=ALIGNED, K=ALIGNED):
     return r, bool(from_input.value)
 
 
-def wgrad_route(dims, fused):
-    r = _lib.mec_internal_wgrad_route(*dims, int(fused))
+def wgrad_route(dims):
+    r = _lib.mec_internal_wgrad_route(*dims)
     assert r >= 0, (dims, r)
     return r
 

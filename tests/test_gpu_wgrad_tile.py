@@ -106,3 +106,22 @@ def test_wgrad_products_left_out(bits):
     got = both(torch.full(dims[:4], x), torch.full((1, 9, 7, 64), x), dims).astype(np.float64)
     ref = 63 * x ** 2
     assert np.abs(got - ref).max() <= 3 * 2.0 ** -24 * ref
+
+
+def test_wgrad_tile_of_a_large_l():
+    """L of more than 2 GiB, I of less: both ways take this kernel, and dK is the same
+    bit for bit; one image's L stays below the limit."""
+    dims = (20, 200, 200, 256, 3, 3, 16, 1, 1)
+    print("[case] wgrad large L", dims, flush=True)
+    g = torch.Generator(device=DEV).manual_seed(54)
+    I = torch.rand(dims[:4], generator=g, device=DEV) - 0.5
+    G = torch.rand((20, 198, 198, 16), generator=g, device=DEV) - 0.5
+    dK = mec.conv2d_wgrad(I, G, 3, 3, 1, 1)
+    L = mec.lower(I, 3, 3, 16, 1, 1)
+    assert L.numel() * 4 > 2 ** 31 > I.numel() * 4
+    dK2 = mec.wgrad_gemm(L, G, 3, dims[2], 1, 1)
+    del L
+    assert torch.equal(dK, dK2)
+    for a, b in ((0, 0), (2, 1)):
+        ref = I[:, a:a + 198, b:b + 198].reshape(-1, 256).double().t().contiguous() @ G.reshape(-1, 16).double()
+        assert (dK[a, b].double() - ref).norm() <= 2e-6 * ref.norm()

@@ -27,3 +27,14 @@ def test_unaligned_routes():
     dims = (32, 224, 224, 64, 7, 7, 64, 2, 2)
     assert k.route(dims, "bf16", "fused", I=k.ALIGNED + 2)[0] == k.FIXED
     assert k.route((32, 227, 227, 3, 11, 11, 96, 4, 4), "bf16", "fused", I=k.ALIGNED + 2)[0] != k.FIRST
+
+
+# (L of more than 2 GiB: from L and from I alike; one image's L of more: neither)
+@pytest.mark.parametrize("dims,want", [
+    ((32, 58, 58, 64, 3, 3, 64, 1, 1), k.WGRAD_TILE),
+    ((20, 200, 200, 256, 3, 3, 16, 1, 1), k.WGRAD_TILE),
+    ((1, 900, 900, 256, 3, 3, 16, 1, 1), k.WGRAD_GENERAL),
+    ((8, 40, 40, 2, 3, 3, 16, 1, 1), k.WGRAD_GENERAL),
+])
+def test_wgrad_routes(dims, want):
+    assert k.wgrad_route(dims) == want
