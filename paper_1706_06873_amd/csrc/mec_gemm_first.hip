@@ -32,7 +32,11 @@ struct FirstParams {
 constexpr int kMaxRows = 512;  // patch rows at most
 constexpr int kFtM = 256, kFtThreads = 256, kFtPixels = 24;  // patch pixels per thread at most
 
-template <int BN>
+// STREAM: O by streaming stores, where a pixel's channels are whole 128-byte lines (3%
+// faster on outputs past 40 MB); lines that two pixels share have to meet in the cache
+// (172x172x3 3x3 -> 60, batch 42: 108 us streaming, 56 through it, 83 the generic tiles;
+// 154x154x1 -> 56, batch 61: 111, 62, 84).
+template <int BN, bool STREAM>
 __global__ __launch_bounds__(kFtThreads, BN == 2 ? 2 : 1) void first_gemm_kernel(FirstParams p) {
     constexpr int TN = 32 * BN, BM = 2;
     extern __shared__ __align__(16) char lds[];  // K, the patch, 16 bytes of zeros
@@ -255,7 +259,7 @@ __global__ __launch_bounds__(kFtThreads, BN == 2 ? 2 : 1) void first_gemm_kernel
 #pragma unroll
                     for (int j = 0; j < BN; ++j) {
                         const float x = acc[i][j][4 * w + e];
-                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), ors, ro[e] + coff[j], 0, 2);
+                        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(uint32_t, x), ors, ro[e] + coff[j], 0, STREAM ? 2 : 0);
                     }
             }
         turn ^= 1;
@@ -358,7 +362,9 @@ hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float
     int64_t groups = fit * cus / p.n_tiles;  // workgroups per channel tile
     if (groups < 1) groups = 1;
     if (groups > tiles) groups = tiles;
-    auto kern = TN == 64 ? first_gemm_kernel<2> : first_gemm_kernel<3>;
+    const bool lines = p.N % 32 == 0;
+    auto kern = TN == 64 ? (lines ? first_gemm_kernel<2, true> : first_gemm_kernel<2, false>)
+                         : (lines ? first_gemm_kernel<3, true> : first_gemm_kernel<3, false>);
     hipLaunchKernelGGL(kern, dim3((uint32_t)(groups * p.n_tiles)), dim3(kFtThreads), bytes, stream, p);
     return hipGetLastError();
 }
