@@ -460,7 +460,7 @@ GemmKernel gemm_route(const Shape& s, const void* A, const void* K, int dtype, b
     if (!layout && gemm_small_preferred(s, dtype, fused)) return GemmKernel::kSmall;
     if (fused && dtype != 0 && !layout && gemm_first_preferred(s, A)) return GemmKernel::kFirst;
     if (fused && dtype != 0 && !layout && gemm_patch_preferred(s, A, K)) return GemmKernel::kPatch;
-    if (dtype == 0 && gemm_tile_preferred(s, fused, layout)) return GemmKernel::kTile;
+    if (dtype == 0 && gemm_tile_preferred(s, A, K, fused, layout)) return GemmKernel::kTile;
     return GemmKernel::kFixed;
 }
 
@@ -468,7 +468,7 @@ GemmKernel gemm_route(const Shape& s, const void* A, const void* K, int dtype, b
 // times), where a kernel that reads I is the faster one.
 bool gemm_from_input(const Shape& s, const void* I, const void* K, int dtype) {
     if (gemm_small_preferred(s, dtype, false)) return false;
-    if (dtype == 0) return gemm_tile_from_input(s);
+    if (dtype == 0) return gemm_tile_from_input(s, I, K);
     return gemm_first_preferred(s, I) || gemm_patch_preferred(s, I, K);
 }
 

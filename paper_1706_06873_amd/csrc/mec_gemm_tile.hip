@@ -522,26 +522,39 @@ bool gemm_tile_holds(const Shape& s, bool fused, const OutLayout* layout) {
 // Taken where it holds the shape, except for
 // * reductions of one chunk, whose time is the tile's start and end (1x1 over 16
 //   and 32 channels: 24 against 19 us and 13.1 against 12.1 for the plain tiles),
-// * few tiles of a long reduction, where the kernels that split it between two
-//   workgroups fill more of the chip (7x7x512 -> 512 at batch 32, 104 tiles: 86
-//   against 60 us; 14x14x256 at batch 1, 12 tiles: 45 against 28; 36 tiles over 36
-//   chunks 24 against 18; 49 over 18 equal),
+// * what the fixed kernels' own tiles (32 pairs x 2 rows x 64 channels, vectors at
+//   16-byte boundaries) do faster; times here / there, in us:
+//   - 3x3 and 5x5 at stride 1 and 7x7 at stride 2, reductions past 640, up to 128 of
+//     their tiles, each of which they give to two workgroups (7x7x512 -> 512 at batch 32
+//     86 / 60; 67x67x288 -> 32 7x7 at batch 8 231 / 187; 32x32x320 -> 528 5x5 131 / 89;
+//     the median of 1600 shapes 0.7 of the time here, past 128 tiles 1.05 to 1.3),
+//   - 3x3 at stride 1 whose runs are not whole chunks of 32, up to a tile per compute
+//     unit (18x18x368 -> 192, batch 19, 66 / 52; of 300 shapes 0.83 to 1.0; with whole
+//     chunks 1.04 to 1.15),
+//   - one-row kernels whose runs end in half a chunk of at most three, from 1600 tiles of
+//     64 x 64 on, where memory bounds both (79x79x80 -> 496 1x1, batch 29, 201 / 169;
+//     52x52x80 -> 224, batch 50, 73 / 66; over 48 channels even),
 // * the ring kernel's layers (7x7 stride 2 over 3 channels 98 against 83 us, 3x3
 //   over 3 channels 91 against 45; 11x11 over 3 channels to 96, batch 128, from L:
 //   248 against 239), but for the tall kernels below from I.
-bool gemm_tile_preferred(const Shape& s, bool fused, const OutLayout* layout) {
+bool gemm_tile_preferred(const Shape& s, const void* A, const void* K, bool fused, const OutLayout* layout) {
     if (!gemm_tile_holds(s, fused, layout)) return false;
-    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R;
+    const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R, n64 = (s.k_c + 63) / 64;
     if (kd <= 32) return false;
-    const bool split_tiles = s.R % 16 == 0 && s.k_c % 4 == 0 &&
-                             ((s.k_h == 3 && s.s_h == 1) || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2));
-    if (split_tiles && kd > 640 && ((M + 63) / 64) * ((s.k_c + 63) / 64) < 112) return false;
+    if (s.R % 16 == 0 && s.k_c % 4 == 0 && !(((uintptr_t)A | (uintptr_t)K) & 15u)) {
+        const int64_t t2 = (s.pairs + 31) / 32 * ((s.o_h + 1) / 2) * n64;  // their tiles
+        const bool k3 = s.k_h == 3 && s.s_h == 1, whole = (fused ? s.R : kd) % 32 == 0;
+        if ((k3 || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2)) && kd > 640 && t2 <= 128 && !layout)
+            return false;
+        if (k3 && !whole && t2 <= 256) return false;
+        if (s.k_h == 1 && s.s_h == 1 && !whole && s.R <= 96 && (M + 63) / 64 * n64 >= 1600) return false;
+    }
     if (gemm_ring_taken(s, 0, fused, layout)) return fused && tall_from_input(s);
     return true;
 }
 
-bool gemm_tile_from_input(const Shape& s) {
-    return gemm_ring_taken(s, 0, false, nullptr) && tall_from_input(s) && gemm_tile_preferred(s, true, nullptr);
+bool gemm_tile_from_input(const Shape& s, const void* I, const void* K) {
+    return gemm_ring_taken(s, 0, false, nullptr) && tall_from_input(s) && gemm_tile_preferred(s, I, K, true, nullptr);
 }
 
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,

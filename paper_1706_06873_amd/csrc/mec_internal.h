@@ -143,9 +143,9 @@ hipError_t launch_gemm_ring(const Shape& s, const void* A, const void* K, float*
 // The slab products on the bf16 matrix cores (mec_gemm_tile.hip): any kernel
 // size, stride and channel count, from L or from I; fp32 as six bf16 products.
 bool gemm_tile_holds(const Shape& s, bool fused, const OutLayout* layout);
-bool gemm_tile_preferred(const Shape& s, bool fused, const OutLayout* layout);
+bool gemm_tile_preferred(const Shape& s, const void* A, const void* K, bool fused, const OutLayout* layout);
 // whether it should read I although L is there
-bool gemm_tile_from_input(const Shape& s);
+bool gemm_tile_from_input(const Shape& s, const void* I, const void* K);
 hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float* O, bool fused,
                             hipStream_t stream, const OutLayout* layout = nullptr);
 

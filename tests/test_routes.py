@@ -23,10 +23,29 @@ def test_product_routes(dims, dtype, algo, want):
     assert k.route(dims, dtype, algo) == want
 
 
+# fp32 shapes that the fixed kernels' 2-row tiles do faster, and their neighbours
+@pytest.mark.parametrize("dims,algo,want", [
+    ((8, 67, 67, 288, 7, 7, 32, 2, 2), "fused", k.FIXED),     # 128 tiles, split in two
+    ((9, 67, 67, 288, 7, 7, 32, 2, 2), "fused", k.TILE),      # 144
+    ((1, 32, 32, 320, 5, 5, 528, 1, 1), "lowered", k.FIXED),  # 126 tiles
+    ((19, 18, 18, 368, 3, 3, 192, 1, 1), "lowered", k.FIXED),  # half chunks, 240 tiles
+    ((19, 18, 18, 384, 3, 3, 192, 1, 1), "lowered", k.TILE),   # whole chunks
+    ((21, 18, 18, 368, 3, 3, 192, 1, 1), "fused", k.TILE),     # half chunks, 264 tiles
+    ((29, 79, 79, 80, 1, 1, 496, 1, 1), "fused", k.FIXED),     # 1x1, two and a half chunks
+    ((2, 79, 79, 80, 1, 1, 496, 1, 1), "fused", k.TILE),       # 1568 tiles
+    ((29, 79, 79, 96, 1, 1, 496, 1, 1), "fused", k.TILE),
+    ((29, 79, 79, 112, 1, 1, 496, 1, 1), "fused", k.TILE),
+])
+def test_fixed_tiles_kept(dims, algo, want):
+    assert k.route(dims, "f32", algo)[0] == want
+
+
 def test_unaligned_routes():
     dims = (32, 224, 224, 64, 7, 7, 64, 2, 2)
     assert k.route(dims, "bf16", "fused", I=k.ALIGNED + 2)[0] == k.FIXED
     assert k.route((32, 227, 227, 3, 11, 11, 96, 4, 4), "bf16", "fused", I=k.ALIGNED + 2)[0] != k.FIRST
+    # the fixed kernels' fast forms need 16-byte vectors
+    assert k.route((19, 18, 18, 368, 3, 3, 192, 1, 1), "f32", "fused", I=k.ALIGNED + 4)[0] == k.TILE
 
 
 # (L of more than 2 GiB: from L and from I alike; one image's L of more: neither)
