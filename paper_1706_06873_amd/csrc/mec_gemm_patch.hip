@@ -348,13 +348,11 @@ hipError_t run_patch(const Shape& s, const void* I, const void* K, float* O, hip
 
 // Taken in bf16 where the kernel has several taps and
 // * its offsets hold the shape (and rows of I and K start on 4-byte boundaries),
-// * at least 0.4 of the chunks' channels and the tiles' output channels exist
-//   (112x112, 3x3 over 18 channels to 30: 36 against 28 us for the generic tiles),
 // * no tile of its own exists for the kernel with these channels (3x3, 5x5 and 1x1
-//   at stride 1 keep theirs: 3x3 over 64 channels 19 against 46 us), or it is the
-//   7x7 stride 2 one and half the compute units get a workgroup (224x224x64 -> 64,
-//   batch 1, 52 workgroups: 30 against 45 us; batch 4, 196: 69 against 43; batch
-//   32: 402 against 258).
+//   at stride 1 keep theirs: 3x3 over 64 channels 19 against 46 us) and at least 0.4 of
+//   the chunks' channels and the tiles' output channels exist (112x112, 3x3 over 18
+//   channels to 30: 36 against 28 us for the generic tiles), or it is the 7x7 stride 2
+//   one and takes longer by patch_beats_k7s2.
 // Against the generic tiles, batch 8 to 64: 3x3 stride 2 over 64 channels 35 -> 26
 // us, over 512 223 -> 90; 3x3 over 100, 90 and 300 channels 89 -> 24, 85 -> 22 and
 // 257 -> 52; 5x5 over 90 186 -> 34; 7x7 stride 2 over 100 at batch 2 406 -> 70.
@@ -368,13 +366,28 @@ bool gemm_patch_holds(const Shape& s, const void* I, const void* K) {
     return pick_patch(s).TH != 0;
 }
 
+// Both kernels' times in us, rounds of workgroups over the compute units times what a
+// round takes; measured on this GPU (they give 91 shapes of 7 to 600 us within 10%, and
+// the faster kernel of each within 5%). Of the fixed tiles those over at most 64 channels
+// are two to a compute unit. 224x224x64 -> 64 (patch / fixed): batch 1 38 / 31, 4 43 / 69,
+// 32 252 / 402; 78x78x16 -> 112, batch 90, 88 / 55; 168x164x48 -> 72, batch 24, 195 / 159.
+static bool patch_beats_k7s2(const Shape& s) {
+    auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
+    const PatchTile t = pick_patch(s);
+    const int64_t tiles = up(s.i_n * s.o_h, t.TH) * up(s.o_w, t.TW) * up(s.k_c, kTN);
+    const double patch = (double)up(tiles, 256) * (0.353 * (double)(s.k_h * s.k_w * up(s.i_c, 32)) + 5.0);
+    const int64_t chunks = up(s.R, 16);
+    if (s.k_c > 64)
+        return patch < (double)up(up(s.pairs, 32) * up(s.o_h, 4) * up(s.k_c, 128), 256) * (1.34 * (double)chunks + 4.2);
+    const int64_t each = up(up(s.pairs, 32) * up(s.o_h, 2), 256);
+    return patch < (double)(each / 2) * (1.25 * (double)chunks + 3.0) + (double)(each % 2) * (1.03 * (double)chunks + 3.0);
+}
+
 bool gemm_patch_preferred(const Shape& s, const void* I, const void* K) {
     if (!gemm_patch_holds(s, I, K)) return false;
-    if (5 * s.i_c * s.k_c < 2 * ((s.i_c + 31) / 32 * 32) * ((s.k_c + 63) / 64 * 64)) return false;
-    const PatchTile t = pick_patch(s);
-    if (launch_gemm_fixed(s, I, K, nullptr, 1, true, nullptr, true) != hipSuccess) return true;
-    const int64_t tiles = ((s.i_n * s.o_h + t.TH - 1) / t.TH) * ((s.o_w + t.TW - 1) / t.TW) * ((s.k_c + kTN - 1) / kTN);
-    return s.k_h == 7 && s.s_h == 2 && tiles >= 128;
+    if (launch_gemm_fixed(s, I, K, nullptr, 1, true, nullptr, true) == hipSuccess)
+        return s.k_h == 7 && s.s_h == 2 && patch_beats_k7s2(s);
+    return 5 * s.i_c * s.k_c >= 2 * ((s.i_c + 31) / 32 * 32) * ((s.k_c + 63) / 64 * 64);
 }
 
 hipError_t launch_gemm_patch(const Shape& s, const void* I, const void* K, float* O, hipStream_t stream) {

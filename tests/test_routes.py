@@ -40,6 +40,20 @@ def test_fixed_tiles_kept(dims, algo, want):
     assert k.route(dims, "f32", algo)[0] == want
 
 
+# bf16 7x7 at stride 2, where the fixed tiles of few input or output channels win
+@pytest.mark.parametrize("dims,want", [
+    ((90, 78, 78, 16, 7, 7, 112, 2, 2), k.FIXED),
+    ((24, 168, 164, 48, 7, 7, 72, 2, 2), k.FIXED),
+    ((90, 78, 78, 32, 7, 7, 112, 2, 2), k.PATCH),
+    ((90, 78, 78, 18, 7, 7, 112, 2, 2), k.PATCH),  # no fixed tile for it
+    ((4, 224, 224, 64, 7, 7, 64, 2, 2), k.PATCH),
+    ((1, 224, 224, 64, 7, 7, 64, 2, 2), k.FIXED),
+])
+@pytest.mark.parametrize("algo", ["lowered", "fused"])
+def test_strided_bf16_routes(dims, algo, want):
+    assert k.route(dims, "bf16", algo)[0] == want
+
+
 def test_unaligned_routes():
     dims = (32, 224, 224, 64, 7, 7, 64, 2, 2)
     assert k.route(dims, "bf16", "fused", I=k.ALIGNED + 2)[0] == k.FIXED
