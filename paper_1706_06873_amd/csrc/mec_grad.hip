@@ -858,8 +858,28 @@ bool wgrad_supported(const Shape& s) {
            wgrad_tiles(s) * wgrad_splits(s) < (int64_t(1) << 31);
 }
 
+// The tile kernel where it holds the shape, but for rows of L that are no whole groups of
+// 8, which it loads element by element where a group spans two (the fp32 kernels / there,
+// in us):
+// * one-row kernels that the slab kernel serves (92x92x164 -> 280 1x1 stride 2, batch 50,
+//   210 / 287; 78x78x204 -> 104 227 / 282; 320 shapes 0.95 on average; 3 and 5 rows 1.2
+//   and 1.35), and three rows where the slab kernel's tiles of 64 rows of L are a fifth
+//   fuller than the 128 rows of dK and the work is long (100x100x20 -> 128, batch 21, 120 /
+//   152; from 2^23 outputs of the forward pass on 0.87 to 1.0, below 0.95 to 1.3),
+// * at most 32 pixels in all, where the time is the tile's start and end (10x7x466 -> 160
+//   7x7 stride 2, batch 6, 12 pixels, 21.5 / 23.4; 180 shapes 0.87 on average).
 WgradKernel wgrad_route(const Shape& s) {
-    return wgrad_tile_holds(s) ? WgradKernel::kTile : wgrad_slab_ok(s) ? WgradKernel::kSlab : WgradKernel::kGeneral;
+    const bool slab = wgrad_slab_ok(s);
+    const WgradKernel fp32 = slab ? WgradKernel::kSlab : WgradKernel::kGeneral;
+    if (!wgrad_tile_holds(s)) return fp32;
+    if (s.R % 8) {
+        const int64_t pixels = s.pairs * s.o_h, KD = s.k_h * s.R;
+        if (pixels <= 32 && !slab) return fp32;
+        if (slab && s.k_h == 1) return fp32;
+        const int64_t tile = (KD + 127) / 128 * 128 * s.R, rows = (s.R + kWs - 1) / kWs * kWs * KD;  // filled rows, crosswise
+        if (slab && s.k_h == 3 && 5 * tile >= 6 * rows && pixels * s.k_c >= (int64_t(1) << 23)) return fp32;
+    }
+    return WgradKernel::kTile;
 }
 
 hipError_t launch_wgrad(const Shape& s, const float* L, const float* G, float* part, float* dK,

@@ -68,6 +68,14 @@ def test_unaligned_routes():
     ((20, 200, 200, 256, 3, 3, 16, 1, 1), k.WGRAD_TILE),
     ((1, 900, 900, 256, 3, 3, 16, 1, 1), k.WGRAD_GENERAL),
     ((8, 40, 40, 2, 3, 3, 16, 1, 1), k.WGRAD_GENERAL),
+    ((50, 92, 92, 164, 1, 1, 280, 2, 2), k.WGRAD_SLAB),        # rows of L no whole groups of 8
+    ((50, 92, 92, 168, 1, 1, 280, 2, 2), k.WGRAD_TILE),
+    ((21, 100, 100, 20, 3, 3, 128, 1, 1), k.WGRAD_SLAB),       # rows of 60: 180 of 256, 60 of 64
+    ((21, 100, 100, 28, 3, 3, 128, 1, 1), k.WGRAD_TILE),       # rows of 84: 252 of 256, 84 of 128
+    ((1, 100, 100, 20, 3, 3, 128, 1, 1), k.WGRAD_TILE),        # short
+    ((21, 100, 100, 20, 5, 5, 128, 1, 1), k.WGRAD_TILE),
+    ((6, 10, 7, 466, 7, 7, 160, 2, 2), k.WGRAD_GENERAL),       # 12 pixels
+    ((20, 10, 7, 466, 7, 7, 160, 2, 2), k.WGRAD_TILE),         # 40
 ])
 def test_wgrad_routes(dims, want):
     assert k.wgrad_route(dims) == want
