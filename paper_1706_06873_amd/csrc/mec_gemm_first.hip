@@ -279,8 +279,9 @@ FirstTile pick_first(const Shape& s, int TN) {
     FirstTile best{0, 0, 0, 0.0};
     const int64_t G = s.i_n * s.o_h, kb = first_k_bytes(s, TN);
     for (int64_t parts = 1; parts <= 16 && parts <= s.o_w; ++parts) {
-        const int64_t TW = (s.o_w + parts - 1) / parts;
+        const int64_t TW = (uint32_t)(s.o_w + parts - 1) / (uint32_t)parts;
         if (TW > kFtM) continue;
+        if ((double)(kFtM / (int32_t)TW * s.o_w) <= best.use * (double)(parts * kFtM)) continue;  // no better however many rows
         for (int64_t TH = kFtM / TW; TH >= 1; TH = TH > 4 ? TH - 1 : TH / 2) {
             const int64_t images = TH > 1 ? (TH - 2) / s.o_h + 2 : 1;
             const int64_t im = images < s.i_n ? images : s.i_n;
@@ -306,18 +307,23 @@ int first_tn(const Shape& s) { return s.k_c <= 64 ? 64 : 96; }
 // stride 4 -> 96 batch 32 83 -> 37 us, batch 1 (49 tiles) 13 against 24; 7x7 stride 2 ->
 // 64 batch 32 81 -> 31; 224x224x3 3x3 -> 64 batch 32 100 -> 81 (its 404 MB of output at
 // 5 TB/s), batch 16 54 -> 44, batch 1 12.3 and 12.7.
-bool gemm_first_holds(const Shape& s, const void* I) {
+static bool first_offsets_hold(const Shape& s, const void* I) {
     if (s.i_c > 4 || s.k_h * s.k_w < 2 || s.s_h > s.k_h || ((uintptr_t)I & 3u)) return false;
     if (s.i_n * s.o_h >= (int64_t(1) << 30) || s.k_h * s.R * s.k_c >= (int64_t(1) << 30)) return false;
     const int64_t images = 256 / s.o_h + 2;
     const int64_t im = images < s.i_n ? images : s.i_n;
     if (im * s.o_h * s.o_w * s.k_c >= (int64_t(1) << 28) || im * s.i_h * s.i_w * s.i_c >= (int64_t(1) << 29)) return false;
-    return pick_first(s, first_tn(s)).TH != 0;
+    return true;
+}
+
+bool gemm_first_holds(const Shape& s, const void* I) {
+    return first_offsets_hold(s, I) && pick_first(s, first_tn(s)).TH != 0;
 }
 
 bool gemm_first_preferred(const Shape& s, const void* I) {
-    if (!gemm_first_holds(s, I)) return false;
+    if (!first_offsets_hold(s, I)) return false;
     const FirstTile t = pick_first(s, first_tn(s));
+    if (!t.TH) return false;
     const int64_t tiles = ((s.i_n * s.o_h + t.TH - 1) / t.TH) * ((s.o_w + t.TW - 1) / t.TW);
     return first_k_bytes(s, first_tn(s)) <= 32 * 1024 || tiles >= 256;
 }
@@ -353,13 +359,10 @@ hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float
     p.div_wt = FastDiv((uint32_t)p.w_tiles);
     p.i_bytes = s.i_n * s.i_h * s.i_w * s.i_c * 2;
     const size_t bytes = (size_t)first_k_bytes(s, TN) + (size_t)t.pixels * 8 + 16;
-    // as many workgroups as stay resident: by LDS, at most two (registers)
-    int dev = 0, cus = 0;
-    if (hipStreamGetDevice(stream, &dev) != hipSuccess ||
-        hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || cus < 1)
-        cus = 256;
+    // as many workgroups as stay resident on the 256 compute units: by LDS, at most two
+    // each (registers); on a device of fewer the rest wait their turn
     const int64_t fit = bytes + 3 * 4 * kFtM + 4 * kMaxRows + 64 <= 80 * 1024 ? 2 : 1;
-    int64_t groups = fit * cus / p.n_tiles;  // workgroups per channel tile
+    int64_t groups = fit * 256 / p.n_tiles;  // workgroups per channel tile
     if (groups < 1) groups = 1;
     if (groups > tiles) groups = tiles;
     const bool lines = p.N % 32 == 0;

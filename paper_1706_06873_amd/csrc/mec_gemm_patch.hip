@@ -298,8 +298,9 @@ PatchTile pick_patch(const Shape& s) {
     PatchTile best{0, 0, 0, 0.0};
     const int64_t G = s.i_n * s.o_h;
     for (int64_t parts = 1; parts <= 16 && parts <= s.o_w; ++parts) {
-        const int64_t TW = (s.o_w + parts - 1) / parts;
+        const int64_t TW = (uint32_t)(s.o_w + parts - 1) / (uint32_t)parts;
         if (TW > kTM) continue;
+        if ((double)(kTM / (int32_t)TW * s.o_w) <= best.use * (double)(parts * kTM)) continue;  // no better however many rows
         for (int64_t TH = kTM / TW; TH >= 1; TH = TH > 4 ? TH - 1 : TH / 2) {
             const int64_t images = TH > 1 ? (TH - 2) / s.o_h + 2 : 1;  // that TH rows can touch
             const int64_t im = images < s.i_n ? images : s.i_n;
@@ -356,14 +357,18 @@ hipError_t run_patch(const Shape& s, const void* I, const void* K, float* O, hip
 // Against the generic tiles, batch 8 to 64: 3x3 stride 2 over 64 channels 35 -> 26
 // us, over 512 223 -> 90; 3x3 over 100, 90 and 300 channels 89 -> 24, 85 -> 22 and
 // 257 -> 52; 5x5 over 90 186 -> 34; 7x7 stride 2 over 100 at batch 2 406 -> 70.
-bool gemm_patch_holds(const Shape& s, const void* I, const void* K) {
+static bool patch_offsets_hold(const Shape& s, const void* I, const void* K) {
     if (s.k_h * s.k_w < 2 || s.s_h > s.k_h || s.i_n * s.o_h >= (int64_t(1) << 30)) return false;
     if (s.k_h * s.R * s.k_c >= (int64_t(1) << 30)) return false;
     const int64_t images = 256 / s.o_h + 2;
     const int64_t im = images < s.i_n ? images : s.i_n;
     if (im * s.o_h * s.o_w * s.k_c >= (int64_t(1) << 28) || im * s.i_h * s.i_w * s.i_c >= (int64_t(1) << 30)) return false;
     if (s.i_c % 2 || s.k_c % 2 || ((uintptr_t)I & 3u) || ((uintptr_t)K & 3u)) return false;
-    return pick_patch(s).TH != 0;
+    return true;
+}
+
+bool gemm_patch_holds(const Shape& s, const void* I, const void* K) {
+    return patch_offsets_hold(s, I, K) && pick_patch(s).TH != 0;
 }
 
 // Both kernels' times in us, rounds of workgroups over the compute units times what a
@@ -371,9 +376,8 @@ bool gemm_patch_holds(const Shape& s, const void* I, const void* K) {
 // the faster kernel of each within 5%). Of the fixed tiles those over at most 64 channels
 // are two to a compute unit. 224x224x64 -> 64 (patch / fixed): batch 1 38 / 31, 4 43 / 69,
 // 32 252 / 402; 78x78x16 -> 112, batch 90, 88 / 55; 168x164x48 -> 72, batch 24, 195 / 159.
-static bool patch_beats_k7s2(const Shape& s) {
+static bool patch_beats_k7s2(const Shape& s, const PatchTile& t) {
     auto up = [](int64_t a, int64_t b) { return (a + b - 1) / b; };
-    const PatchTile t = pick_patch(s);
     const int64_t tiles = up(s.i_n * s.o_h, t.TH) * up(s.o_w, t.TW) * up(s.k_c, kTN);
     const double patch = (double)up(tiles, 256) * (0.353 * (double)(s.k_h * s.k_w * up(s.i_c, 32)) + 5.0);
     const int64_t chunks = up(s.R, 16);
@@ -384,9 +388,12 @@ static bool patch_beats_k7s2(const Shape& s) {
 }
 
 bool gemm_patch_preferred(const Shape& s, const void* I, const void* K) {
-    if (!gemm_patch_holds(s, I, K)) return false;
-    if (launch_gemm_fixed(s, I, K, nullptr, 1, true, nullptr, true) == hipSuccess)
-        return s.k_h == 7 && s.s_h == 2 && patch_beats_k7s2(s);
+    if (!patch_offsets_hold(s, I, K)) return false;
+    const bool fixed = launch_gemm_fixed(s, I, K, nullptr, 1, true, nullptr, true) == hipSuccess;
+    if (fixed && (s.k_h != 7 || s.s_h != 2)) return false;
+    const PatchTile t = pick_patch(s);
+    if (!t.TH) return false;
+    if (fixed) return patch_beats_k7s2(s, t);
     return 5 * s.i_c * s.k_c >= 2 * ((s.i_c + 31) / 32 * 32) * ((s.k_c + 63) / 64 * 64);
 }
 

@@ -282,14 +282,17 @@ bool wgrad_tile_holds(const Shape& s) {
 // compute unit's chunks (two workgroups at a time, 1.2 us a chunk for the two, 0.8
 // alone, 6 us to start and end) plus the partial sums' write and read-back.
 int64_t wgrad_tile_splits(const Shape& s, int64_t room) {
-    const int64_t chunks = (s.i_n * s.o_h * s.o_w + kPix - 1) / kPix;
+    const uint32_t chunks = (uint32_t)((s.i_n * s.o_h * s.o_w + kPix - 1) / kPix);  // the pixels fit 29 bits
     const int64_t tiles = ((s.k_h * s.R + kJ - 1) / kJ) * ((s.k_c + kM - 1) / kM);
-    int64_t best = 1;
+    const double sums = 8.0 * (double)(s.k_h * s.R * s.k_c);
+    uint32_t best = 1;
     double best_t = 0.0;
-    for (int64_t sp = 1; sp <= room && sp <= chunks; ++sp) {
-        const int64_t busiest = (tiles * sp + 255) / 256, each = (chunks + sp - 1) / sp;
-        const double t = (double)(busiest / 2) * ((double)each * 1.2 + 6.0) + (double)(busiest % 2) * ((double)each * 0.8 + 6.0) +
-                         (double)sp * 8.0 * (double)(s.k_h * s.R * s.k_c) / 5.0e6;
+    for (uint32_t sp = 1; sp <= (uint32_t)room && sp <= chunks; ++sp) {  // (a loop per call: 32-bit divisions, no more than needed)
+        const double sums_t = (double)sp * sums / 5.0e6;
+        if (sp > 1 && sums_t >= best_t) break;  // it only grows
+        const int64_t busiest = (tiles * sp + 255) / 256;
+        const uint32_t each = (chunks + sp - 1) / sp;
+        const double t = (double)(busiest / 2) * ((double)each * 1.2 + 6.0) + (double)(busiest % 2) * ((double)each * 0.8 + 6.0) + sums_t;
         if (sp == 1 || t < best_t) {
             best = sp;
             best_t = t;
