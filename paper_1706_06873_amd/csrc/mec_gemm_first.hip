@@ -25,7 +25,7 @@ struct FirstParams {
     int32_t G, o_h, o_w, i_h, i_w, i_c, k_h, k_w, N, s_h, s_w;
     int32_t TH, TW, PW, pixels, pairs, kw2;  // pairs of taps in all, per kernel row
     int32_t w_tiles, n_tiles, tiles;         // tiles: of output pixels
-    FastDiv div_oh, div_ow, div_TW, div_PW, div_kw2, div_wt;
+    FastDiv div_oh, div_TW, div_PW, div_kw2, div_wt;
     int64_t i_bytes;
 };
 
@@ -352,7 +352,6 @@ hipError_t launch_gemm_first(const Shape& s, const void* I, const void* K, float
     if (tiles * p.n_tiles > 0x7fffffff) return hipErrorInvalidValue;
     p.tiles = (int32_t)tiles;
     p.div_oh = FastDiv((uint32_t)p.o_h);
-    p.div_ow = FastDiv((uint32_t)p.o_w);
     p.div_TW = FastDiv((uint32_t)p.TW);
     p.div_PW = FastDiv((uint32_t)p.PW);
     p.div_kw2 = FastDiv((uint32_t)p.kw2);

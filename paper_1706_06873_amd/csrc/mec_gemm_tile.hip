@@ -53,12 +53,12 @@ struct TileParams {
 };
 
 // BM x BN 32x32 blocks per wave, WM x WN waves. RUN: every run is whole chunks
-// (seglen a multiple of 32), so a chunk's addresses are uniform.
-template <int BM, int BN, int WM, int WN, bool RUN, int MODE>
+// (seglen a multiple of 32), so a chunk's addresses are uniform. ONE: one chunk at a time
+// in registers, which the largest tile's accumulators leave no room beside, and the
+// compiler's own schedule.
+template <int BM, int BN, int WM, int WN, bool RUN, bool ONE>
 struct TileCfg {
-    static constexpr bool kSched = MODE & 1;
-    static constexpr bool kOne = MODE & 2;
-    static constexpr int kVALU = 6;
+    static constexpr bool kOne = ONE;
     // waves per SIMD that the LDS admits, for the register allocation
     static constexpr int kWaves = BM * BN == 4 ? (WM * WN == 8 ? 2 : 1) : BM * BN == 2 ? 2 : 3;
     static constexpr int kBM = BM, kBN = BN, kWM = WM, kWN = WN;
@@ -298,13 +298,11 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
         __builtin_amdgcn_sched_barrier(0);
         stage(now, nxt);
         products(f0);
-        if constexpr (C::kSched) {
 #pragma unroll
-            for (int s = 0; s < 6 * BM * BN; ++s) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, C::kVALU, 0);  // VALU
-                __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
-            }
+        for (int s = 0; s < 6 * BM * BN; ++s) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 6, 0);  // VALU
+            __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
         }
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
@@ -313,13 +311,11 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
         __builtin_amdgcn_sched_barrier(0);
         load(now);
         products(f1);
-        if constexpr (C::kSched) {
 #pragma unroll
-            for (int s = 0; s < 6 * BM * BN; ++s) {
-                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
-                __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global read
-            }
+        for (int s = 0; s < 6 * BM * BN; ++s) {
+            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
+            __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
+            __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global read
         }
         __builtin_amdgcn_sched_barrier(0);
     };
@@ -333,28 +329,9 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
             read(f0, cur, 0);
             stage(r, nxt);
             products(f0);
-            if constexpr (C::kSched) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 3 * (BM + BN), 0);  // LDS read
-#pragma unroll
-                for (int s = 0; s < 6 * BM * BN; ++s) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, C::kVALU, 0);  // VALU
-                    __builtin_amdgcn_sched_group_barrier(0x200, 1, 0);  // LDS write
-                }
-                __builtin_amdgcn_sched_barrier(0);
-            }
             read(f0, cur, 1);
             load(r);
             products(f0);
-            if constexpr (C::kSched) {
-                __builtin_amdgcn_sched_group_barrier(0x100, 3 * (BM + BN), 0);  // LDS read
-#pragma unroll
-                for (int s = 0; s < 6 * BM * BN; ++s) {
-                    __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);  // MFMA
-                    __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);  // VALU
-                    __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);  // global read
-                }
-            }
             __syncthreads();
         };
         for (int c = 0; c < p.nchunks; c += 2) {
@@ -362,18 +339,18 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
             one(lds + C::STAGE, lds);
         }
     } else {
-    Regs r0, r1;
-    load(r0);
-    load(r1);
-    stage(r0, lds);
-    load(r0);
-    __syncthreads();
-    read(f0, lds, 0);
-    // r1 holds chunk c + 1, r0 chunk c + 2
-    for (int c = 0; c < p.nchunks; c += 2) {
-        step(r1, lds, lds + C::STAGE);
-        step(r0, lds + C::STAGE, lds);
-    }
+        Regs r0, r1;
+        load(r0);
+        load(r1);
+        stage(r0, lds);
+        load(r0);
+        __syncthreads();
+        read(f0, lds, 0);
+        // r1 holds chunk c + 1, r0 chunk c + 2
+        for (int c = 0; c < p.nchunks; c += 2) {
+            step(r1, lds, lds + C::STAGE);
+            step(r0, lds + C::STAGE, lds);
+        }
     }
 
     // Values the split does not hold (see the top). Rows and columns past the last
@@ -435,10 +412,10 @@ __global__ __launch_bounds__(C::THREADS, C::kWaves) void tile_gemm_f32_kernel(Ti
         }
 }
 
-template <int BM, int BN, int WM, int WN, int SCHED, bool ANY = true>
+template <int BM, int BN, int WM, int WN, bool ONE = false, bool ANY = true>
 hipError_t run_tile(TileParams p, hipStream_t stream) {
-    using CA = TileCfg<BM, BN, WM, WN, true, SCHED>;
-    using CR = TileCfg<BM, BN, WM, WN, false, SCHED>;
+    using CA = TileCfg<BM, BN, WM, WN, true, ONE>;
+    using CR = TileCfg<BM, BN, WM, WN, false, ONE>;
     p.n_tiles = (p.N + CA::TN - 1) / CA::TN;
     const int64_t ntiles = ((int64_t)p.M + CA::TM - 1) / CA::TM * p.n_tiles;
     if (ntiles > 0x7fffffff) return hipErrorInvalidValue;
@@ -460,7 +437,9 @@ hipError_t run_tile(TileParams p, hipStream_t stream) {
 // (one), 2 128x64 (two), 3 64x64 (three). The busiest compute unit takes
 // ceil(tiles / 256) of them, as many at a time as fit; a chunk costs the times
 // below with 1, 2, 3 resident, a tile's start and end the last figure, all in us
-// and measured on this GPU (they give 18 shapes of 20 to 450 us within 7%).
+// and measured on this GPU on long reductions over whole chunks. Of 14000 shapes past 15
+// us the model gives 0.85 to 1.2 of the time there, down to 0.7 where runs are gathered
+// and 0.6 below 400 terms; it has to order the tiles, not to time them.
 // Runs that are not whole chunks leave out 128x128, whose gathering loads spill
 // registers (11x11 over 3 channels at batch 32: 226 us, 70 in 256x128).
 int pick_tile(int64_t M, int64_t N, int64_t nchunks, bool run) {
@@ -595,10 +574,10 @@ hipError_t launch_gemm_tile(const Shape& s, const void* A, const void* K, float*
     p.groups = (int32_t)((p.kd + 7) / 8);
     p.div_seg = FastDiv((uint32_t)p.seglen);
     switch (pick_tile(p.M, p.N, (p.groups + 3) / 4, p.seglen % 32 == 0)) {
-        case 0: return run_tile<2, 2, 4, 2, 2>(p, stream);
-        case 1: return run_tile<2, 2, 2, 2, 1, false>(p, stream);
-        case 2: return run_tile<1, 2, 4, 1, 1>(p, stream);
-        default: return run_tile<1, 1, 2, 2, 1>(p, stream);
+        case 0: return run_tile<2, 2, 4, 2, true>(p, stream);
+        case 1: return run_tile<2, 2, 2, 2, false, false>(p, stream);
+        case 2: return run_tile<1, 2, 4, 1>(p, stream);
+        default: return run_tile<1, 1, 2, 2>(p, stream);
     }
 }
 

@@ -25,7 +25,7 @@ struct WgradTileParams {
     float* part;
     uint32_t P;      // output pixels
     int32_t KD, N;   // k_h * R, k_c
-    int32_t seglen, nseg;   // runs of the window, as in mec_gemm_tile.hip
+    int32_t seglen;  // of the window's runs, as in mec_gemm_tile.hip
     uint32_t xstride;
     uint32_t a_n, a_h, a_w; // source elements per step of n, h, w
     FastDiv div_ow, div_oh, div_seg;
@@ -311,7 +311,6 @@ hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, flo
     p.KD = (int32_t)(s.k_h * s.R);
     p.N = (int32_t)s.k_c;
     if (fused) {
-        p.nseg = (int32_t)s.k_h;
         p.seglen = (int32_t)s.R;
         p.xstride = (uint32_t)(s.i_w * s.i_c);
         p.a_n = (uint32_t)(s.i_h * s.i_w * s.i_c);
@@ -319,7 +318,6 @@ hipError_t launch_wgrad_tile(const Shape& s, const float* A, const float* G, flo
         p.a_w = (uint32_t)(s.s_w * s.i_c);
         p.a_bytes = s.i_n * s.i_h * s.i_w * s.i_c * 4;
     } else {
-        p.nseg = 1;
         p.seglen = p.KD;
         p.xstride = 0;
         p.a_n = (uint32_t)(s.o_w * s.i_h * s.R);
