@@ -1,4 +1,7 @@
-"""The bf16 products over at most 4 input channels: bit for bit on integers."""
+"""The bf16 products over at most 4 input channels: bit for bit on integers.
+
+The entry points give some of these shapes to other kernels; test_gpu_kernels.py calls
+this one itself on all of them."""
 import numpy as np
 import pytest
 import torch
@@ -17,8 +20,8 @@ CASES = [
     (5, 9, 8, 1, 5, 4, 97, 1, 2),       # one channel, even kernel rows, two channel tiles
     (2, 40, 21, 2, 2, 1, 33, 2, 1),     # two channels, one tap a row: half of each pair is padding
     (7, 3, 260, 4, 3, 3, 40, 3, 2),     # one output row per image, several column ranges
-    (66, 57, 57, 3, 11, 11, 96, 4, 4),  # K of 101 KB, more tiles than one per compute unit
-    (300, 20, 20, 3, 5, 5, 32, 2, 2),   # workgroups that take several tiles
+    (66, 57, 57, 3, 11, 11, 96, 4, 4),  # K of 101 KB
+    (300, 20, 20, 3, 5, 5, 32, 2, 2),   # many tiles, K of 20 KB
 ]
 
 

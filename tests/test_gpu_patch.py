@@ -2,6 +2,9 @@
 
 Integers are exact, so O must match the oracle bit for bit; on floats the fp32
 accumulators over exact bf16 products stay well inside 2e-6.
+
+The entry points give some of these shapes to other kernels; test_gpu_kernels.py calls
+this one itself on all of them.
 """
 import numpy as np
 import pytest

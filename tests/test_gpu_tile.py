@@ -4,6 +4,9 @@ Small integers split and sum exactly, so O must match the oracle bit for bit.
 On floats the bar is the split's own: the six products leave out at most
 2^-24 of each product, and the sums are the fp32 accumulators', so O stays
 within a few fp32 roundings per sum of the 64-bit result, well inside 2e-6.
+
+The entry points give some of these shapes to other kernels; test_gpu_kernels.py calls
+this one itself on all of them.
 """
 import numpy as np
 import pytest
