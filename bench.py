@@ -5,9 +5,9 @@
 
 One step is one MEC convolution of the layer on inputs already resident in
 device memory: the compact lowering of I into L followed by the o_h slab
-products (mec_lower + mec_gemm, exactly the two kernels
-mec_conv2d(MEC_ALGO_LOWERED) enqueues), or the fused kernel
-(mec_conv2d(MEC_ALGO_FUSED)). The default layer is the largest fp32 one,
+products from L (mec_lower + mec_gemm; mec_conv2d(MEC_ALGO_LOWERED) takes the
+products from I where that is faster, for instance on the default layer), or the
+fused kernel (mec_conv2d(MEC_ALGO_FUSED)). The default layer is the largest fp32 one,
 AlexNet conv1 (i_n=128, 227x227x3, 11x11x96 kernel, stride 4), from L.
 Every operand a kernel reads rotates over at least 512 MB of buffer sets
 (twice the 256 MB memory-attached last-level cache), so that no launch finds
@@ -42,6 +42,9 @@ sys.path.insert(0, REPO)
 
 METRIC = "effective conv TFLOP/s (2·MAC/time) + workspace bytes vs im2col, 1×MI355X"
 PEAK_TFLOPS = {"f32": 157.3, "bf16": 2516.6}   # dense MFMA peaks of the MI355X
+PEAK_F32_AS_BF16 = PEAK_TFLOPS["bf16"] / 6     # fp32 products as six bf16 products each
+KERNELS = ("small_gemm_kernel", "first_gemm_kernel", "patch_gemm_kernel", "tile_gemm_f32_kernel",
+           "slab_gemm_%s_*kernel")              # in the order of the library's routes
 PEAK_HBM_GBS = 8000.0
 DEFAULT_LAYER = "alexnet_conv1"
 MIN_ROTATION_BYTES = 1 << 30   # bytes each kernel's rotating buffers span, at least
@@ -121,6 +124,25 @@ def load_traffic(dtype, layer_name, algo, digest):
                                               t["write_kib"] * t["write_scale"]) * 1024))
                         out[key + "_kernel"] = t.get("kernel")
     return out
+
+
+def products_kernel(mec, dims, dtype, algo):
+    """(name, MFMA peak in TFLOP/s) of the kernel that computes the products a
+    step times: mec_gemm's from L or from the im2col matrix, or the fused one's.
+    Buffers are taken as aligned."""
+    import ctypes
+    i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w = dims
+    if algo == "im2col":  # the 1x1 convolution over pixels that carry the patches
+        o_h, o_w = mec.output_dims(i_h, i_w, k_h, k_w, s_h, s_w)
+        dims = (i_n, o_h, o_w, k_h * k_w * i_c, 1, 1, k_c, 1, 1)
+    aligned = ctypes.c_void_p(1 << 20)
+    route = mec.lib.mec_internal_gemm_route(aligned, aligned, *dims, mec.BF16 if dtype == "bf16" else mec.F32,
+                                            mec.FUSED if algo == "fused" else -1, None)
+    if route < 0:
+        raise RuntimeError("no kernel for %r" % (dims,))
+    name = KERNELS[route]
+    return (name % dtype if "%" in name else name,
+            PEAK_F32_AS_BF16 if name == "tile_gemm_f32_kernel" else PEAK_TFLOPS[dtype])
 
 
 def rotation_sets(nbytes, nsets):
@@ -264,11 +286,11 @@ def measure(cfg, HipEvent, steps, warmup, digest, settle_s):
         prod_ms = timed(HipEvent, cfg.stream, cfg.products, cfg, steps)
 
     layer = cfg.layer
-    peak = PEAK_TFLOPS[layer.dtype]
+    family, peak = products_kernel(cfg.mec, cfg.dims, layer.dtype, cfg.algo)
     traffic = load_traffic(layer.dtype, layer.name, cfg.algo, digest)
     # the kernel's own name where the layer's profile (taken on these sources)
     # recorded it, else its family
-    kname = traffic["products_kernel"] or "slab_gemm_%s_*kernel" % layer.dtype
+    kname = traffic["products_kernel"] or family
     kname += {"fused": " (from I)", "im2col": " (im2col product, k_h = 1)", "lowered": ""}[cfg.algo]
     ab = cfg.alg_bytes()
     ridge = peak * 1e12 / (PEAK_HBM_GBS * 1e9)

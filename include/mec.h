@@ -53,7 +53,8 @@ extern "C" {
 enum mec_dtype { MEC_F32 = 0, MEC_BF16 = 1 };
 
 /* MEC_ALGO_LOWERED: Algorithm 2 as two kernels -- the lowering writes L into
- *   the caller's workspace, then the slab products read it.
+ *   the caller's workspace, then the slab products form O from it, or from I
+ *   where a kernel that reads I is the faster one (see mec_conv2d).
  * MEC_ALGO_FUSED: one kernel forms each slab of L in on-chip memory straight
  *   from I; L is never written to device memory and no workspace is used.
  * MEC_ALGO_IM2COL: the baseline MEC replaces (Section 3.1): im2col lowering
@@ -120,13 +121,17 @@ int mec_lower(const void* I, void* L,
  * output of mec_lower for the same arguments. O must not overlap L or K.
  * Results are reproducible run to run: each output's summation order is fixed
  * by the shape and by whether L, K and O are 16-byte aligned (alignment selects
- * the staging path, and fp32 tiles staged straight into LDS sum their products
- * in another order, within rounding of the others). (For 3x3 layers whose
- * tiles leave compute units idle, each tile's reduction is split in two halves
- * that are added into O after O is zeroed; two partial sums added to zero
- * commute exactly.) Every kernel height runs: where no tile of its own fits,
- * the windows L[n, w][s_h*R*h : s_h*R*h + k_h*R] are read as the rows of one
- * plain product (Section 3.2's flat view).
+ * the kernel and its staging path; each sums its products in an order of its
+ * own, within rounding of the others). Most fp32 shapes run on the bf16 matrix
+ * cores, each product as six bf16 products of the operands' three-way split,
+ * within fp32's own rounding; values that the split does not hold (infinities,
+ * NaNs, below 2^-110) come out as plain fp32 products give them. Shapes of few
+ * outputs share each output's reduction between the waves of a workgroup. (For
+ * 3x3, 5x5 and 7x7 layers whose tiles leave compute units idle, each tile's
+ * reduction may be split in two halves that are added into O after O is zeroed;
+ * two partial sums added to zero commute exactly.) Every kernel height runs:
+ * where no tile of its own fits, the windows L[n, w][s_h*R*h : s_h*R*h + k_h*R]
+ * are read as the rows of one plain product (Section 3.2's flat view).
  * Returns MEC_OK or a negative status. */
 int mec_gemm(const void* L, const void* K, float* O,
              int i_n, int i_h, int i_w, int i_c,
@@ -150,10 +155,14 @@ int mec_im2col(const void* I, void* M,
                int dtype, void* stream);
 
 /* The convolution O = I * K by MEC (Algorithm 2), or by the im2col baseline.
- * MEC_ALGO_LOWERED: mec_lower into `workspace`, then mec_gemm from it;
+ * MEC_ALGO_LOWERED: mec_lower into `workspace`, then the slab products: from
+ *   L, as mec_gemm computes them, or from I (fp32 kernels of 9 and more rows
+ *   over few channels, strided, unaligned and few-channel bf16 layers), whose O
+ *   then equals mec_gemm's within rounding but not bit for bit;
  *   workspace_bytes must be >= mec_workspace_bytes(..., MEC_ALGO_LOWERED) and
  *   the workspace must be aligned to the element size. On return (after the
- *   stream completes) the workspace holds L exactly as mec_lower writes it.
+ *   stream completes) the workspace holds L exactly as mec_lower writes it,
+ *   either way.
  * MEC_ALGO_FUSED: one kernel; workspace may be NULL and is not touched. Its
  *   tiles stage the slab rows from I on chip, so kernels taller than they hold
  *   are refused with MEC_ERR_UNSUPPORTED (MEC_ALGO_LOWERED takes them).

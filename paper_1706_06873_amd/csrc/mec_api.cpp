@@ -326,8 +326,9 @@ int mec_internal_gemm_route(const void* I, const void* K, int i_n, int i_h, int 
     mec::Shape s;
     const int rc = make_shape(s, i_n, i_h, i_w, i_c, k_h, k_w, k_c, s_h, s_w);
     if (rc != MEC_OK) return rc;
-    if (!valid_dtype(dtype) || (algo != MEC_ALGO_LOWERED && algo != MEC_ALGO_FUSED)) return MEC_ERR_INVALID_ARG;
-    const bool fused = algo == MEC_ALGO_FUSED || mec::gemm_from_input(s, I, K, dtype);
+    if (!valid_dtype(dtype) || (algo != MEC_ALGO_LOWERED && algo != MEC_ALGO_FUSED && algo != -1))
+        return MEC_ERR_INVALID_ARG;
+    const bool fused = algo == MEC_ALGO_FUSED || (algo == MEC_ALGO_LOWERED && mec::gemm_from_input(s, I, K, dtype));
     if (from_input) *from_input = fused;
     return (int)mec::gemm_route(s, I, K, dtype, fused, nullptr);
 }

@@ -219,8 +219,9 @@ hipError_t noalloc_scratch(hipStream_t stream, void** ptr);
 }  // namespace mec
 
 // For the tests, which load the library through the public header's ABI; not part of it.
-// The kernel (GemmKernel, WgradKernel) that mec_conv2d and the weight gradient take, and
-// *from_input whether the products read I; nothing is launched and no pointer read.
+// The kernel (GemmKernel, WgradKernel) that mec_conv2d (algo -1: mec_gemm, I is L then)
+// and the weight gradient take, and *from_input whether the products read I; nothing is
+// launched and no pointer read. bench.py names the kernels it times by it.
 extern "C" int mec_internal_gemm_route(const void* I, const void* K, int i_n, int i_h, int i_w, int i_c, int k_h, int k_w,
                                        int k_c, int s_h, int s_w, int dtype, int algo, int* from_input);
 extern "C" int mec_internal_wgrad_route(int i_n, int i_h, int i_w, int i_c, int k_h, int k_w, int k_c, int s_h, int s_w);

@@ -21,10 +21,10 @@ _lib.mec_internal_dgrad_gemm.argtypes = [_i, _vp, _vp, _vp] + [_i] * 9 + [_vp]
 
 
 def route(dims, dtype="f32", algo="lowered", I=ALIGNED, K=ALIGNED):
-    """(the kernel that conv2d's products take, whether they read I)."""
+    """(the kernel that the products of conv2d, or of gemm, take, whether they read I)."""
     from_input = _i(0)
     code = mec.F32 if dtype == "f32" else mec.BF16
-    kind = mec.LOWERED if algo == "lowered" else mec.FUSED
+    kind = {"lowered": mec.LOWERED, "fused": mec.FUSED, "gemm": -1}[algo]
     r = _lib.mec_internal_gemm_route(I, K, *dims, code, kind, ctypes.byref(from_input))
     assert r >= 0, (dims, r)
     return r, bool(from_input.value)

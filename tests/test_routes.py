@@ -79,3 +79,22 @@ def test_unaligned_routes():
 ])
 def test_wgrad_routes(dims, want):
     assert k.wgrad_route(dims) == want
+
+
+# what bench.py calls the kernel that it times, and the peak that it holds it against
+@pytest.mark.parametrize("name,algo,kernel,six", [
+    ("resnet_mid", "lowered", "tile_gemm_f32_kernel", True),
+    ("resnet_mid", "fused", "tile_gemm_f32_kernel", True),
+    ("alexnet_conv1", "lowered", "slab_gemm_f32_*kernel", False),  # mec_gemm from L: the ring
+    ("alexnet_conv1", "fused", "tile_gemm_f32_kernel", True),
+    ("vgg_first", "fused", "slab_gemm_f32_*kernel", False),
+    ("deep_bf16", "lowered", "slab_gemm_bf16_*kernel", False),
+    ("resnet_mid", "im2col", "tile_gemm_f32_kernel", True),
+])
+def test_bench_names_the_kernel(name, algo, kernel, six):
+    import bench
+    import paper_1706_06873_amd as mec
+    layer = wl.LAYERS[name]
+    got, peak = bench.products_kernel(mec, layer.dims, layer.dtype, algo)
+    assert got == kernel
+    assert peak == (bench.PEAK_TFLOPS["bf16"] / 6 if six else bench.PEAK_TFLOPS[layer.dtype])
