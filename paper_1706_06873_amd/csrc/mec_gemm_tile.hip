@@ -474,9 +474,11 @@ int pick_tile(int64_t M, int64_t N, int64_t nchunks, bool run) {
 // 19.6 / 12.8, 32 57.9 / 43.2, 128 181 / 156; 9x9 14.3 / 10.6 to 131 / 116), past 96,
 // which the ring takes in two passes, always (100 channels: 143 / 74, 9x9 103 / 57),
 // between them, where a fourth of a 128-channel tile is empty, with at most 160 tiles
-// (batch 1 25.5 / 12.6, 4 26.8 / 17.4) or full rounds of them (batch 128 245 / 237;
-// 338 tiles in two rounds 66.6 / 71.6, 189 tiles of 9x9 30.5 / 31.8). Up to 32
-// channels the ring leads from batch 16 on (120 / 147 at 128).
+// (batch 1 25.5 / 12.6, 4 26.8 / 17.4) or full rounds of them (batch 128 245 / 237): over
+// the batches of two rounds and more the ring takes 1.02 to 1.08 of the time here where
+// tiles fill at least 0.8 of their rounds, 0.95 where 0.5 to 0.75. One round of 161 to 256
+// tiles lies near even (1.02 to 1.12). Up to 32 channels the ring leads from batch 16 on
+// (120 / 147 at 128).
 static bool tall_from_input(const Shape& s) {
     if (s.k_h < 9 || s.R < 24 || s.k_c <= 32 || s.k_c > 128) return false;
     if (s.k_c <= 64 || s.k_c > 96) return true;
