@@ -11,9 +11,9 @@
 // to LDS. 128 rows x 64 columns per workgroup, two stages, two workgroups per
 // compute unit. Rows of dL that no tap reaches (s_h > k_h) come out as zeros.
 // Like the other split tiles it is bound by splitting and writing to LDS. dI (with
-// the fold) against the fp32 kernel: 57x57x64 -> 128 3x3 stride 2, batch 16, 66 -> 38
-// us; 24x24x96 -> 256 5x5, batch 32, 406 -> 155; 29x31x37 -> 61 5x5 79 -> 23; 227x227x3
-// -> 96 11x11 stride 4, batch 128, 2394 -> 544.
+// the fold) against the fp32 kernel: 57x57x64 -> 128 3x3 stride 2, batch 16, 66 -> 36
+// us; 24x24x96 -> 256 5x5, batch 32, 416 -> 161; 29x31x37 -> 61 5x5, batch 16, 86 -> 34;
+// 227x227x3 -> 96 11x11 stride 4, batch 128, 2387 -> 600.
 #include "mec_split.h"
 
 namespace mec {

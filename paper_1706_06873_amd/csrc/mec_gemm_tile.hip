@@ -19,7 +19,7 @@
 // matrix cores cut sums off at about 2^-24 of the largest addend where the fp32
 // instruction rounds each of its steps, so the five small products go to
 // accumulators of their own, added once at the end. Measured against 64 bits
-// (reductions of 32 to 32768 terms; signed, non-negative and constant values): 0.3-0.6
+// (reductions of 32 to 32768 terms; signed, non-negative and constant values): 0.2-0.5
 // of the fp32 instruction's error, and less on constants.
 // Not finite or very small values: an infinity or NaN in a window, and a sum
 // that leaves fp32's range, leave infinities or NaNs in the accumulators, and

@@ -9,9 +9,10 @@
 // chunks of 32 pixels through two stages of LDS, two workgroups per compute unit.
 // What bounds it is splitting and writing 192 columns to LDS per chunk beside 24
 // matrix instructions a wave. Against the fp32 kernels, whole gradient (products and
-// the shares' sum), batch 32: 58x58x64 -> 64 100 -> 69 us, 112x112x64 -> 128 545 ->
-// 389, 28x28x128 98 -> 57, 14x14x256 78 -> 49, 24x24x96 -> 256 5x5 180 -> 117,
-// 224x224x64 -> 64 7x7 1708 -> 960; errors against 64 bits 0.4-0.7 of theirs. The
+// the shares' sum), batch 32: 58x58x64 -> 64 101 -> 70 us, 112x112x64 -> 128 561 ->
+// 417, 28x28x128 99 -> 58, 14x14x256 83 -> 52, 24x24x96 -> 256 5x5 181 -> 130,
+// 224x224x64 -> 64 7x7 1695 -> 982; errors against 64 bits 0.35-0.55 of theirs, on
+// operands of one sign to 0.8. The
 // windows' offsets are worked out once per chunk by one wave (83 us on the first of
 // these with every thread dividing for itself).
 #include "mec_split.h"
