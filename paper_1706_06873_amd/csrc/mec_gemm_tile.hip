@@ -508,10 +508,13 @@ bool gemm_tile_holds(const Shape& s, bool fused, const OutLayout* layout) {
 //   - 3x3 and 5x5 at stride 1 and 7x7 at stride 2, reductions past 640, up to 128 of
 //     their tiles, each of which they give to two workgroups (7x7x512 -> 512 at batch 32
 //     86 / 60; 67x67x288 -> 32 7x7 at batch 8 231 / 187; 32x32x320 -> 528 5x5 131 / 89;
-//     the median of 1600 shapes 0.7 of the time here, past 128 tiles 1.05 to 1.3),
-//   - 3x3 at stride 1 whose runs are not whole chunks of 32, up to a tile per compute
-//     unit (18x18x368 -> 192, batch 19, 66 / 52; of 300 shapes 0.83 to 1.0; with whole
-//     chunks 1.04 to 1.15),
+//     the median of 1600 shapes 0.7 of the time here, past 128 tiles 1.05 to 1.3). Rows
+//     that are no multiples of 16 go through registers there: past 1280 (7x7x420 -> 84
+//     3x3, batch 109, 76 / 56; of 150 shapes 0.62 to 0.96, below 1280 to 1.45),
+//   - 3x3 at stride 1, and 5x5 from I, whose runs are not whole chunks of 32, up to a
+//     tile per compute unit (18x18x368 -> 192 3x3, batch 19, 66 / 52; of 300 shapes 0.83
+//     to 1.0; 18x18x48 -> 160 5x5, batch 16, 26.3 / 25.1; of 136 shapes 0.88 to 0.99, from
+//     L 1.03 to 1.22; with whole chunks 1.04 to 1.15),
 //   - one-row kernels whose runs end in half a chunk of at most three, from 1600 tiles of
 //     64 x 64 on, where memory bounds both (79x79x80 -> 496 1x1, batch 29, 201 / 169;
 //     52x52x80 -> 224, batch 50, 73 / 66; over 48 channels even),
@@ -522,13 +525,13 @@ bool gemm_tile_preferred(const Shape& s, const void* A, const void* K, bool fuse
     if (!gemm_tile_holds(s, fused, layout)) return false;
     const int64_t M = s.i_n * s.o_h * s.o_w, kd = s.k_h * s.R, n64 = (s.k_c + 63) / 64;
     if (kd <= 32) return false;
-    if (s.R % 16 == 0 && s.k_c % 4 == 0 && !(((uintptr_t)A | (uintptr_t)K) & 15u)) {
+    if (s.R % 4 == 0 && !(fused && s.i_c % 4) && s.k_c % 4 == 0 && !(((uintptr_t)A | (uintptr_t)K) & 15u)) {
         const int64_t t2 = (s.pairs + 31) / 32 * ((s.o_h + 1) / 2) * n64;  // their tiles
-        const bool k3 = s.k_h == 3 && s.s_h == 1, whole = (fused ? s.R : kd) % 32 == 0;
-        if ((k3 || (s.k_h == 5 && s.s_h == 1) || (s.k_h == 7 && s.s_h == 2)) && kd > 640 && t2 <= 128 && !layout)
-            return false;
-        if (k3 && !whole && t2 <= 256) return false;
-        if (s.k_h == 1 && s.s_h == 1 && !whole && s.R <= 96 && (M + 63) / 64 * n64 >= 1600) return false;
+        const bool k3 = s.k_h == 3 && s.s_h == 1, k5 = s.k_h == 5 && s.s_h == 1, k7 = s.k_h == 7 && s.s_h == 2;
+        const bool whole = (fused ? s.R : kd) % 32 == 0, r16 = s.R % 16 == 0;
+        if ((k3 || k5 || k7) && kd > (r16 ? 640 : 1280) && t2 <= 128 && !layout) return false;
+        if ((k3 || (k5 && fused && !layout)) && r16 && !whole && t2 <= 256) return false;
+        if (r16 && s.k_h == 1 && s.s_h == 1 && !whole && s.R <= 96 && (M + 63) / 64 * n64 >= 1600) return false;
     }
     if (gemm_ring_taken(s, 0, fused, layout)) return fused && tall_from_input(s);
     return true;

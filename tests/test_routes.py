@@ -28,6 +28,17 @@ def test_product_routes(dims, dtype, algo, want):
     ((8, 67, 67, 288, 7, 7, 32, 2, 2), "fused", k.FIXED),     # 128 tiles, split in two
     ((9, 67, 67, 288, 7, 7, 32, 2, 2), "fused", k.TILE),      # 144
     ((1, 32, 32, 320, 5, 5, 528, 1, 1), "lowered", k.FIXED),  # 126 tiles
+    ((109, 7, 7, 420, 3, 3, 84, 1, 1), "fused", k.FIXED),     # rows of 1260, 108 tiles
+    ((109, 7, 7, 420, 3, 3, 84, 1, 1), "lowered", k.FIXED),
+    ((109, 7, 7, 418, 3, 3, 84, 1, 1), "fused", k.TILE),      # rows of 1254, no vectors of 4
+    ((109, 7, 7, 140, 3, 3, 84, 1, 1), "fused", k.TILE),      # reduction of 1260
+    ((109, 7, 7, 420, 3, 3, 96, 1, 1), "lowered", k.FIXED),
+    ((140, 7, 7, 420, 3, 3, 84, 1, 1), "fused", k.TILE),      # 132 tiles
+    ((2, 40, 240, 2, 3, 200, 128, 1, 1), "lowered", k.FIXED),  # vectors of 4 in L
+    ((2, 40, 240, 2, 3, 200, 128, 1, 1), "fused", k.TILE),    # but not in I
+    ((1, 93, 93, 496, 5, 5, 32, 1, 1), "fused", k.FIXED),     # 5x5 half chunks, 135 tiles
+    ((1, 93, 93, 496, 5, 5, 32, 1, 1), "lowered", k.TILE),
+    ((1, 93, 93, 480, 5, 5, 32, 1, 1), "fused", k.TILE),      # whole chunks
     ((19, 18, 18, 368, 3, 3, 192, 1, 1), "lowered", k.FIXED),  # half chunks, 240 tiles
     ((19, 18, 18, 384, 3, 3, 192, 1, 1), "lowered", k.TILE),   # whole chunks
     ((21, 18, 18, 368, 3, 3, 192, 1, 1), "fused", k.TILE),     # half chunks, 264 tiles
